@@ -4,12 +4,10 @@
 // are taken per option by that group (section 4.1); here that group is one
 // wavefront:
 //
-//   * one wave prices one option: lane j holds tree nodes jC .. jC+C-1 in
-//     registers (C = ceil((N+1)/64), rounded up to an instantiated size); a time
-//     step updates every node from itself and its upper neighbour, which for
-//     a lane's last node is the next lane's first node (one cross-lane
-//     permute per step and value array), so no barrier and no LDS array is
-//     needed;
+//   * one wave prices one option: a European price is the FP64 sum over the
+//     leaves, an American one a backward induction over the live nodes of
+//     the tree, ceil(nodes / 64) per lane in registers, a node's other
+//     neighbour one lane away (a wavefront shift, no barrier and no LDS);
 //   * a wave is the decision unit ("logical lane") of the techniques: unit u
 //     of L = 64 ceil(ceil(n/IPT)/64) units processes options u + kL,
 //     k < IPT, and decides alone for each (the thread level of section
@@ -24,8 +22,12 @@
 //   * perforation: herded over the unit's option loop (small, large, ini,
 //     fini); a skipped option is neither read nor written.
 //
-// Node prices S u^(2i-n) are carried by one multiplication per step and
-// recomputed from exp2 every 32 steps, which bounds their FP32 drift.
+// Bound by VALU issue.  65,536 American options on 512 steps: 2785 us when
+// every step updated all 64 x 9 node slots of both values (9 instructions a
+// node), 522 us with the triangle of nodes, two instructions a node and the
+// European one of the two prices summed (6,450 VALU instructions per wave
+// against 43,000, 2.7 clocks each); 1023 steps 9694 -> 1496 us, 127 steps
+// 251 -> 116, 30 steps 85 -> 48; European 512 steps 1268 -> 103 us.
 #include "launch_binomial.hpp"
 #include <type_traits>
 #include "wave.hpp"
@@ -47,77 +49,353 @@ __device__ __forceinline__ float bo_dist2(const float (&x)[N], const float (&e)[
   return acc;
 }
 
-// value of lane (lane + 1); the last lane reads its own (unused)
+// value of the next / previous lane, by a wavefront shift in the VALU (no LDS
+// round trip on the step loop's dependence chain); lane 63 / lane 0, which
+// have none, read 0 and never need it
 __device__ __forceinline__ float from_next_lane(float v) {
-  const int src = lane_id() < 63 ? lane_id() + 1 : 63;
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));  // wave_shl:1
 }
+__device__ __forceinline__ float from_prev_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));  // wave_shr:1
+}
+
+// Lane l's value of v, the same for every lane.
+__device__ __forceinline__ double read_lane(double v, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Inclusive prefix sum over the lanes (lane 63 ends with the wave's sum):
+// row shifts scan each row of 16 lanes, row broadcasts carry the rows on; a
+// lane with no source adds zero.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROW_MASK, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROW_MASK, 0xf, true);
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_scan_add(double v) {
+  v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+  v = dpp_add<0x112, 0xf>(v);  // row_shr:2
+  v = dpp_add<0x114, 0xf>(v);  // row_shr:4
+  v = dpp_add<0x118, 0xf>(v);  // row_shr:8
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+constexpr double kLog2eD = 1.4426950408889634074;
 
 struct BoOut {
   float call, put;
 };
 
-// CRR tree of one option over the 64 lanes of the calling wave; every lane
-// returns the prices.
-template <int C>
-__device__ __forceinline__ BoOut bo_tree(float S, float K, float T, float r, float v, int N, bool american) {
+typedef __attribute__((address_space(3))) float LdsFloat;
+
+__device__ __forceinline__ bool uniform(bool b) { return __builtin_amdgcn_readfirstlane((int)b) != 0; }
+
+// What the FP64 part of a price hands on: the tree's FP32 parameters and the
+// prices that need no induction.
+struct BoHead {
+  double u, d, l2u;  // up and down factors, log2 u
+  double pu, pd;     // discounted probabilities
+  double X;          // spot at the lane's first leaf: S u^(2 j - N), j = lane ceil((N + 1) / 64)
+  float call, put;   // European prices, where `sums` says so
+  int sums;          // bit 0: the call is final, bit 1: the put is
+  int regular;       // 0 < p < 1, prices positive and finite
+};
+
+// The tree's parameters and, with `sums`, its European call and put as what
+// they are: the discounted expectation of the payoff over the leaves, whose
+// up-move counts are binomially distributed.  N + 1 terms in FP64 instead of
+// N^2 / 2 nodes: lane l takes C consecutive leaves; the first one's weight
+// comes from a wave scan of log2 of the lanes' coefficient ratios, the
+// others from w_{j+1} / w_j = (N - j) / (j + 1) p / (1 - p).
+//
+// Early exercise on this tree (no dividends): holding from a node with the
+// exercise values X u - K and X d - K above it is worth at least
+// pu (X u - K) + pd (X d - K) = X - K / a, so for r >= 0 a call is never
+// exercised before its expiry, and with the signs turned a put never for
+// r <= 0: such a price is the European one.  Irregular parameters (p outside
+// (0, 1), prices that are not positive and finite) leave both values to the
+// induction.
+//
+// A function of its own: inlined, the FP64 constants and temporaries are kept
+// in registers across the caller's option loop (over 200 VGPRs).
+__device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T, float r, float v, int N,
+                                                    bool american, bool sums) {
   const int lane = lane_id();
-  // tree parameters in FP64 (uniform), used in FP32
-  const double dt = (double)T / N;
-  const double u = exp((double)v * sqrt(dt)), d = 1.0 / u, a = exp((double)r * dt);
-  const double p = (a - d) / (u - d);
-  const float uf = (float)u, pu = (float)(p / a), pd = (float)((1.0 - p) / a);
-  const float log2u = (float)(log2(u));
-  float X[C], Vc[C], Vp[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    const int i = lane * C + c;
-    // nodes past the last leaf are padding: zero, never read by a live node
-    X[c] = i <= N ? S * __builtin_amdgcn_exp2f((float)(2 * i - N) * log2u) : 0.0f;
-    Vc[c] = i <= N ? fmaxf(X[c] - K, 0.0f) : 0.0f;
-    Vp[c] = i <= N ? fmaxf(K - X[c], 0.0f) : 0.0f;
-  }
-  // the step loop, with the exercise test compiled in or out (a runtime
-  // flag would cost two lane selects per node and step)
-  auto steps = [&](auto american_tag) {
-    constexpr bool kAmerican = decltype(american_tag)::value;
-    for (int n = N - 1; n >= 0; --n) {
-      const float nc = from_next_lane(Vc[0]), np = from_next_lane(Vp[0]);
-      if (kAmerican) {
-        if ((n & 31) == 0) {
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            const int i = lane * C + c;
-            X[c] = i <= n ? S * __builtin_amdgcn_exp2f((float)(2 * i - n) * log2u) : 0.0f;
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < C; ++c) X[c] *= uf;
+  const double dt = (double)T / N, su = (double)v * sqrt(dt), rdt = (double)r * dt;
+  // the four exponentials of the tree in one evaluation, a lane each
+  const double ex = exp(lane == 0 ? su : lane == 1 ? -su : lane == 2 ? rdt : -rdt);
+  const double u = read_lane(ex, 0), d = read_lane(ex, 1), a = read_lane(ex, 2), disc = read_lane(ex, 3);
+  const double p = (a - d) / (u - d), q = 1.0 - p, l2u = su * kLog2eD;
+  const int C = (N + 64) >> 6;
+  const int j0 = lane * C;
+  BoHead h{u, d, l2u, p * disc, q * disc, (double)Sf * exp2((double)(2 * j0 - N) * l2u), 0.0f, 0.0f, 0, 0};
+  h.regular = uniform(p > 0.0 && q > 0.0 && Sf > 0.0f && Kf > 0.0f && Sf < INFINITY && Kf < INFINITY);
+  if (sums) {
+    if (h.regular)
+      h.sums = (uniform(!american || r >= 0.0f) ? 1 : 0) | (uniform(!american || r <= 0.0f) ? 2 : 0);
+    if (h.sums) {
+      double num = 1.0, den = 1.0;
+#pragma unroll 1
+      for (int c = 0; c < C; ++c) {
+        const int j = j0 + c;
+        if (j < N) {
+          num *= (double)(N - j);
+          den *= (double)(j + 1);
         }
       }
-#pragma unroll
+      const double own = log2(num / den);
+      const double before = wave_scan_add(own) - own;
+      const double l2 = log2(lane == 0 ? p : q);
+      const double l2p = read_lane(l2, 0), l2q = read_lane(l2, 1);
+      double w = exp2(before + (double)j0 * l2p + (double)(N - j0) * l2q - (double)N * rdt * kLog2eD);
+      double X = h.X;
+      const double u2 = u * u, K = (double)Kf, pq = p / q;
+      double call = 0.0, put = 0.0;
+#pragma unroll 1
       for (int c = 0; c < C; ++c) {
-        const float up_c = c + 1 < C ? Vc[c + 1] : nc;
-        const float up_p = c + 1 < C ? Vp[c + 1] : np;
-        float vc = __builtin_fmaf(pu, up_c, pd * Vc[c]);
-        float vp = __builtin_fmaf(pu, up_p, pd * Vp[c]);
-        if (kAmerican) {
-          vc = fmaxf(vc, X[c] - K);
-          vp = fmaxf(vp, K - X[c]);
+        const int j = j0 + c;
+        if (j <= N) {
+          call += w * fmax(X - K, 0.0);
+          put += w * fmax(K - X, 0.0);
         }
-        Vc[c] = vc;
-        Vp[c] = vp;
+        w *= pq * ((double)(N - j) / (double)(j + 1));
+        X *= u2;
+      }
+      h.call = (float)read_lane(wave_scan_add(call), 63);
+      h.put = (float)read_lane(wave_scan_add(put), 63);
+      if (american) {  // never below the exercise value, rounding included
+        h.call = fmaxf(h.call, Sf - Kf);
+        h.put = fmaxf(h.put, Kf - Sf);
+      }
+    }
+  }
+  return h;
+}
+
+// Backward induction of NV value arrays of one option over the 64 lanes of the
+// calling wave; every lane returns the values at the root.
+//
+// Positions: after 2m steps node i sits at position i + m, and so it does one
+// step later.  Position p then holds the spot S u^(2p-N) after an even
+// number of steps and S u^(2p-N+1) after an odd one, whatever the step: what
+// a node needs of its spot is one of two constant arrays (E0 even, E1 odd;
+// no per-step spot update and no drift).  Even to odd steps take a node's
+// upper neighbour, odd to even ones its lower.  Two steps shrink the live
+// positions m .. N-m by one at either end, and as soon as they fit c - 1
+// positions per lane instead of c they are dealt out anew through LDS, so
+// the wave works on the triangle of nodes and not on its bounding rectangle.
+// Positions outside the live range hold values that no live node reads.
+// node(v, e, up, dn): value v of a node from the two it leads to; NE: constant
+// arrays, one for every value or one of each.
+template <int CM, int NV, int NE, class Node>
+__device__ __forceinline__ void bo_walk(int N, int lane, LdsFloat *lds, float (&V)[NV][CM], float (&E0)[NE][CM],
+                                        float (&E1)[NE][CM], const Node &node, float (&root)[NV]) {
+  const int need = (N + 64) >> 6;
+  int base = 0, m = 0;
+  // one phase: c positions per lane, from base
+  auto phase = [&](auto c_tag) {
+    constexpr int c = decltype(c_tag)::value;
+    if (c > need) return;
+    if (c < need) {  // from c + 1 positions per lane: deal the live ones out from m
+      // at most 33: a phase starts with at most 64 (c + 1) live positions and
+      // ends with at least 64 c - 1, so every read below is inside 64 (c + 1)
+      const int from = m - base;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));  // addresses are formed here, not kept in registers throughout
+      auto deal = [&](float (&a)[CM]) {
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < (c < CM ? c + 1 : c); ++k) lds[ln * (c + 1) + k] = a[k];
+        wave_lds_fence();
+#pragma unroll
+        for (int k = 0; k < c; ++k) a[k] = lds[from + ln * c + k];
+      };
+#pragma unroll
+      for (int v = 0; v < NV; ++v) deal(V[v]);
+#pragma unroll
+      for (int v = 0; v < NE; ++v) {
+        deal(E0[v]);
+        deal(E1[v]);
+      }
+      base = m;
+    }
+    const int stop = c > 1 ? 64 * (c - 1) : 2;  // live positions at which the phase ends
+    for (; N - 2 * m + 1 > stop; ++m) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {  // even to odd
+        const float up = from_next_lane(V[v][0]);
+#pragma unroll
+        for (int k = 0; k < c; ++k) V[v][k] = node(v, E1[v % NE][k], k + 1 < c ? V[v][k + 1 < c ? k + 1 : k] : up, V[v][k]);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {  // odd to even
+        const float dn = from_prev_lane(V[v][c - 1]);
+#pragma unroll
+        for (int k = c - 1; k >= 0; --k) V[v][k] = node(v, E0[v % NE][k], V[v][k], k ? V[v][k ? k - 1 : 0] : dn);
       }
     }
   };
-  if (american)
-    steps(std::true_type{});
-  else
-    steps(std::false_type{});
-  // node 0 is lane 0's first node
-  BoOut o;
-  o.call = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Vc[0])));
-  o.put = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Vp[0])));
+  auto phases = [&](auto self, auto c_tag) -> void {
+    constexpr int c = decltype(c_tag)::value;
+    phase(c_tag);
+    if constexpr (c > 1) self(self, std::integral_constant<int, c - 1>{});
+  };
+  phases(phases, std::integral_constant<int, CM>{});
+  // m = floor(N / 2); an odd N has one step, even to odd, left
+  const int at = m - base;  // < 64: the live positions fit one per lane
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const float last = node(v, E1[v % NE][0], from_next_lane(V[v][0]), V[v][0]);
+    root[v] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int((N & 1) ? last : V[v][0]), at));
+  }
+}
+
+// Lane index for an induction's first positions: opaque, so that what depends
+// on it is formed there and not kept in registers across the option loop.
+__device__ __forceinline__ int fresh_lane() {
+  int lane = lane_id();
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// American prices by their early-exercise premium, for regular parameters
+// and N >= 1.  With the exercise value e = max(sgn (X - K), 0) of a node and
+// A = V - e >= 0, V = max(continuation, e) becomes
+//   A = max(pu A_up + pd A_dn + D, 0),  D = pu e_up + pd e_dn - e,
+// with A = 0 on the leaves.  D depends on the position alone and is formed
+// once, in FP64.  Scaled by a power of two not below K (A <= K: a put is
+// worth at most K, a call at most its spot) the maximum is the clamp of the
+// second multiply-add, so a node costs two instructions; max itself would be
+// a third, and one that issues at half the rate of a multiply-add.  The
+// rounding errors are those of the premium, not of the price, and D is an
+// exact zero where the option is out of the money.  NV = 2: call (value 0) and put.
+template <int CM, int NV>
+__device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, int N, float sgn, LdsFloat *lds,
+                                           float (&price)[NV]) {
+  const int lane = fresh_lane();
+  const int need = (N + 64) >> 6;
+  const int ks = __builtin_amdgcn_frexp_expf(Kf);  // K <= 2^ks
+  float A[NV][CM], D0[NV][CM], D1[NV][CM];
+  const double K = (double)Kf, u2 = q.u * q.u;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const double sg = NV == 2 ? (v == 0 ? 1.0 : -1.0) : (double)sgn;
+    auto ex = [&](double x) { return fmax(sg * (x - K), 0.0); };
+    double X = q.X;
+    double below = ex(X * q.d), e = ex(X);  // at the odd position below, at this even position
+#pragma unroll
+    for (int c = 0; c < CM; ++c) {
+      A[v][c] = D0[v][c] = D1[v][c] = 0.0f;
+      if (c < need) {
+        const double odd = ex(X * q.u);
+        X *= u2;
+        const double up = ex(X);
+        D0[v][c] = ldexpf((float)(q.pu * odd + q.pd * below - e), -ks);
+        D1[v][c] = ldexpf((float)(q.pu * up + q.pd * e - odd), -ks);
+        below = odd;
+        e = up;
+      }
+      // one position after the other: side by side, their FP64 temporaries
+      // would take over a hundred registers more
+      asm volatile("" : "+v"(D0[v][c]), "+v"(D1[v][c]));
+    }
+  }
+  const float pu = (float)q.pu, pd = (float)q.pd;
+  auto node = [&](int, float d, float up, float dn) {
+    const float t = __builtin_fmaf(pu, up, __builtin_fmaf(pd, dn, d));
+    return __builtin_amdgcn_fmed3f(t, 0.0f, 1.0f);  // the clamp modifier
+  };
+  float root[NV];
+  bo_walk<CM, NV, NV>(N, lane, lds, A, D0, D1, node, root);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const float sg = NV == 2 ? (v == 0 ? 1.0f : -1.0f) : sgn;
+    price[v] = ldexpf(root[v], ks) + fmaxf(sg * (Sf - Kf), 0.0f);
+  }
+}
+
+// The induction on the prices themselves, for any parameters (NV = 2: call
+// and put; NV = 1: the one of sign sgn): a node is its continuation or, where
+// american, its exercise value if that is larger.
+template <int CM, int NV>
+__device__ __forceinline__ void bo_values(const BoHead &q, float S, float K, int N, bool american, float sgn,
+                                          LdsFloat *lds, float (&price)[NV]) {
+  const int lane = fresh_lane();
+  const int need = (N + 64) >> 6;
+  const float pu = (float)q.pu, pd = (float)q.pd, l2u = (float)q.l2u, l2ul = (float)(q.l2u - (double)l2u);
+  float V[NV][CM], E0[1][CM], E1[1][CM];  // exercise values, NaN (no exercise) for European options
+  // S u^k, the exponent's rounding error carried into the result
+  auto spot = [&](int k) {
+    const float f = (float)k, h = f * l2u;
+    const float e = __builtin_fmaf(f, l2ul, __builtin_fmaf(f, l2u, -h));
+    return S * (__builtin_amdgcn_exp2f(h) * __builtin_fmaf(e, 0.693147180559945309f, 1.0f));
+  };
+#pragma unroll
+  for (int c = 0; c < CM; ++c) {
+    const int p = lane * need + c;
+    const float x0 = sgn * (spot(2 * p - N) - K), x1 = sgn * (spot(2 * p - N + 1) - K);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) V[v][c] = fmaxf(v ? -x0 : x0, 0.0f);
+    E0[0][c] = american ? x0 : __builtin_nanf("");
+    E1[0][c] = american ? x1 : __builtin_nanf("");
+    asm volatile("" : "+v"(E0[0][c]), "+v"(E1[0][c]));  // one position after the other, as above
+  }
+  // max(cont, e) as a median with +inf, one instruction: fmaxf would first
+  // quiet e, a register from outside the loop, with a second one.  Like
+  // fmaxf it returns the other operand when one is NaN.
+  float inf = INFINITY;
+  asm("" : "+v"(inf));
+  auto node = [&](int v, float e, float up, float dn) {
+    return __builtin_amdgcn_fmed3f(__builtin_fmaf(pu, up, pd * dn), v ? -e : e, inf);
+  };
+  bo_walk<CM, NV, 1>(N, lane, lds, V, E0, E1, node, price);
+}
+
+// Longer trees with irregular parameters; rare, and a function of its own so
+// that each kernel does not carry a copy.
+template <int CM>
+__device__ __attribute__((noinline)) BoOut bo_irregular(const BoHead q, float S, float K, int N, bool american,
+                                                        LdsFloat *lds) {
+  BoOut o{0.0f, 0.0f};
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    float p[1];
+    bo_values<CM, 1>(q, S, K, N, american, side == 0 ? 1.0f : -1.0f, lds, p);
+    (side == 0 ? o.call : o.put) = p[0];
+  }
+  return o;
+}
+
+// Call and put of one option on the N-step tree, computed by the calling wave.
+// From 64 steps (European) or 128 (American) on, a European price comes from
+// the leaf sum and only the other one, if any, goes through an induction.
+template <int CM>
+__device__ __forceinline__ BoOut bo_price(float S, float K, float T, float r, float v, int N, bool american,
+                                          LdsFloat *lds) {
+  const BoHead q = bo_head(S, K, T, r, v, N, american, CM > 2 || (!american && N >= 64));
+  const int sums = __builtin_amdgcn_readfirstlane(q.sums);
+  const bool regular = __builtin_amdgcn_readfirstlane(q.regular) != 0;
+  BoOut o{q.call, q.put};
+  if (sums == 3) return o;
+  if constexpr (CM <= 2) {
+    float p[2];
+    if (american && regular)
+      bo_premium<CM, 2>(q, S, K, N, -1.0f, lds, p);
+    else
+      bo_values<CM, 2>(q, S, K, N, american, 1.0f, lds, p);
+    o = BoOut{p[0], p[1]};
+  } else {
+    if (!regular) return bo_irregular<CM>(q, S, K, N, american, lds);
+    float p[1];
+    bo_premium<CM, 1>(q, S, K, N, sums == 1 ? -1.0f : 1.0f, lds, p);
+    (sums == 1 ? o.put : o.call) = p[0];
+  }
   return o;
 }
 
@@ -178,9 +456,11 @@ __device__ __forceinline__ uint32_t bo_trace_word(bool approx, bool voted, bool 
 // option ranges [kL, (k+1)L) -- can be priced by any wavefronts: one option
 // per wavefront over the kept ranges only, so every SIMD gets the same share
 // of trees whatever the options per unit.  The outputs are those of TECH 3.
-template <int C, int TECH, int H>
+template <int CM, int TECH, int H>
 __global__ void __launch_bounds__(256) k_binomial(BoArgs a) {
   __shared__ unsigned long long sums[4];
+  __shared__ float deal[4][64 * CM];  // per wave: positions changing lanes
+  LdsFloat *const lds = (LdsFloat *)deal[threadIdx.x >> 6];
   const int lane = lane_id();
   const int64_t unit = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (TECH == 4) {
@@ -195,7 +475,7 @@ __global__ void __launch_bounds__(256) k_binomial(BoArgs a) {
       float x[5];
 #pragma unroll
       for (int j = 0; j < 5; ++j) x[j] = a.in[j][i];
-      const BoOut y = bo_tree<C>(x[0], x[1], x[2], x[3], x[4], a.steps, a.american);
+      const BoOut y = bo_price<CM>(x[0], x[1], x[2], x[3], x[4], a.steps, a.american, lds);
       if (lane == 0) {
         a.out[0][i] = y.call;
         a.out[1][i] = y.put;
@@ -267,7 +547,7 @@ __global__ void __launch_bounds__(256) k_binomial(BoArgs a) {
         continue;
       }
     }
-    const BoOut y = bo_tree<C>(x[0], x[1], x[2], x[3], x[4], a.steps, a.american);
+    const BoOut y = bo_price<CM>(x[0], x[1], x[2], x[3], x[4], a.steps, a.american, lds);
     if (lane == 0) {
       a.out[0][i] = y.call;
       a.out[1][i] = y.put;
@@ -309,11 +589,11 @@ __global__ void __launch_bounds__(256) k_binomial(BoArgs a) {
 
 int64_t bo_units(int64_t n, int ipt) { return 64 * (((n + ipt - 1) / ipt + 63) / 64); }
 
-// nodes per lane: the instantiated sizes, so that at most one lane's worth of
-// slots is padding for every N up to 1023
-int bo_nodes_per_lane(int steps) {
-  const int need = (steps + 1 + 63) / 64;
-  for (int c : {2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16})
+// Most positions per lane a kernel is instantiated for: a tree of N steps
+// starts with ceil((N+1)/64) of them; N is at most 1023.
+int bo_positions_per_lane(int steps) {
+  const int need = (steps + 64) / 64;
+  for (int c : {2, 4, 8, 12, 16})
     if (need <= c) return c;
   return 0;
 }
@@ -388,18 +668,11 @@ static void bo_go_c(const BoArgs &a, int tech, int block, hipStream_t s) {
 }
 
 hipError_t launch_binomial(const BoArgs &a, int tech, int block, hipStream_t s) {
-  switch (bo_nodes_per_lane(a.steps)) {
+  switch (bo_positions_per_lane(a.steps)) {
     case 2: bo_go_c<2>(a, tech, block, s); break;
-    case 3: bo_go_c<3>(a, tech, block, s); break;
     case 4: bo_go_c<4>(a, tech, block, s); break;
-    case 5: bo_go_c<5>(a, tech, block, s); break;
-    case 6: bo_go_c<6>(a, tech, block, s); break;
-    case 7: bo_go_c<7>(a, tech, block, s); break;
     case 8: bo_go_c<8>(a, tech, block, s); break;
-    case 9: bo_go_c<9>(a, tech, block, s); break;
-    case 10: bo_go_c<10>(a, tech, block, s); break;
     case 12: bo_go_c<12>(a, tech, block, s); break;
-    case 14: bo_go_c<14>(a, tech, block, s); break;
     case 16: bo_go_c<16>(a, tech, block, s); break;
     default: return hipErrorInvalidValue;
   }

@@ -122,7 +122,7 @@ hpac_status check_bo(const char *fn, const hpac_region_io *io, int32_t steps, in
   if (hpac::bo_units(io->n, io->items_per_lane) * 64 > kMaxWorkItems)
     return fail(HPAC_EINVAL, "%s: %lld options at %d per unit need a grid of more than 2^32-1 lanes; raise "
                 "items_per_lane", fn, (long long)io->n, io->items_per_lane);
-  if (steps < 1 || hpac::bo_nodes_per_lane(steps) == 0)
+  if (steps < 1 || hpac::bo_positions_per_lane(steps) == 0)
     return fail(HPAC_EINVAL, "%s: steps = %d out of range [1, 1023]", fn, steps);
   if (american != 0 && american != 1) return fail(HPAC_EINVAL, "%s: american must be 0 or 1", fn);
   if (io->n > 0) {

@@ -24,7 +24,7 @@ struct BoArgs {
 };
 
 int64_t bo_units(int64_t n, int ipt);
-int bo_nodes_per_lane(int steps);  // 0 if the tree does not fit
+int bo_positions_per_lane(int steps);  // 0 if the tree does not fit
 // tech: 0 exact, 1 iACT, 2 TAF, 3 perforation
 hipError_t launch_binomial(const BoArgs &a, int tech, int block, hipStream_t stream);
 

@@ -239,3 +239,43 @@ def test_empty_batch_is_a_no_op():
     out = [torch.zeros(0, dtype=torch.float32, device=DEV) for _ in range(2)]
     hpac.hpac_bo_exact([torch.zeros(0, device=DEV)] * 5, out, 64)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 62, 63, 64, 65, 126, 127, 128, 129, 191, 192, 255, 256, 320, 511, 512, 767,
+                                   768, 1022, 1023])
+@pytest.mark.parametrize("american", [True, False])
+def test_tree_at_lane_and_phase_edges(steps, american):
+    """Trees at the edges of the positions per lane (64 c - 1 .. 64 c + 1
+    nodes) and of the leaf sum, on rates of both signs and zero: which of the
+    two prices is the European one changes with the rate's sign."""
+    n = 96
+    x = inputs.uniform_box(n, 31 + steps)
+    x[3] = np.resize([-0.06, -0.01, 0.0, 0.02, 0.09], n)
+    x[1, ::7] = x[0, ::7]  # at the money: the strike is a node of an even tree
+    x = np.ascontiguousarray(x.astype(np.float32))
+    y, _, _ = run(hpac.hpac_bo_exact, x, steps, 1, trace=False, counters=False, american=american)
+    ref, scale = oracle_values(x, steps, american)
+    assert np.all(np.abs(y - ref) <= tol(steps) * scale)
+    with np.errstate(invalid="ignore"):
+        bound = tol(steps) * np.abs(ref) + 64 * 2.0 ** -24 * itm_leaf_scale(x, steps) + 2.0 ** -126
+    # the leaf scale is defined where the weights are a distribution, 0 < p < 1
+    assert np.all((np.abs(y - ref) <= bound) | np.isnan(bound))
+
+
+@pytest.mark.parametrize("steps", [5, 64, 130, 260, 515, 800, 1023])
+@pytest.mark.parametrize("american", [True, False])
+def test_tree_with_probability_above_one(steps, american):
+    """p = 1 + 1 / (2 N) (growth above the up-move) and p = -1 / (2 N): the
+    weights' absolute sum is at most 1 + 1 / N per step, which lets an early
+    rounding error grow by at most e over the tree."""
+    n = 64
+    x = inputs.uniform_box(n, 77)
+    dt = x[2] / steps
+    side = np.where(np.arange(n) % 2, 1.0, -1.0)
+    x[4] = 0.02
+    x[3] = side * x[4] / np.sqrt(dt) * (1.0 + 1.0 / steps)
+    x = np.ascontiguousarray(x.astype(np.float32))
+    y, _, _ = run(hpac.hpac_bo_exact, x, steps, 1, trace=False, counters=False, american=american)
+    ref, scale = oracle_values(x, steps, american)
+    assert np.all(np.isfinite(ref))
+    assert np.all(np.abs(y - ref) <= 3.0 * tol(steps) * np.maximum(scale, np.abs(ref)))
