@@ -93,6 +93,50 @@ def test_adam_step():
     assert np.allclose(w.cpu().numpy(), wr, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 129])
+def test_training_gradient_of_each_workgroup(n):
+    """Every workgroup's partial gradient and loss at the edges of the 16-item
+    tiles and of the 64-item workgroups: FP32 sums of at most 64 items through
+    three products of depth 64, against the oracle on those items alone."""
+    x = inputs.uniform_box(n, seed=52).astype(np.float32)
+    C, Pp, _, _ = oracle.bs_price(*x)
+    t = np.stack([C, Pp]).astype(np.float32)
+    nm = dict(norm_for(t.astype(np.float64)), out_scale=np.array([3.0, 20.0]))
+    w = f32(surrogate.init_params(4))
+    w[320:384] = f32(np.linspace(-0.5, 0.5, 64))
+    nb = hpac.hpac_mlp_grad_blocks(n)
+    gp = torch.full((nb * P,), float("nan"), dtype=torch.float32, device=DEV)
+    lp = torch.full((nb,), float("nan"), dtype=torch.float32, device=DEV)
+    hpac.hpac_mlp_grad(dev_cols(x), dev_cols(t), torch.from_numpy(w.astype(np.float32)).to(DEV),
+                       hpac.make_norm(**nm), n, gp, lp)
+    torch.cuda.synchronize()
+    g, loss = gp.view(nb, P).double().cpu().numpy(), lp.double().cpu().numpy()
+    for b in range(nb):
+        s = slice(64 * b, min(64 * b + 64, n))
+        k = s.stop - s.start
+        l_ref, g_ref = oracle.mlp_loss_grad(x[:, s], t[:, s], w, {q: f32(v) for q, v in nm.items()})
+        assert abs(loss[b] / (2 * k) - l_ref) <= 1e-4 * l_ref
+        g_ref = g_ref * (k / n)
+        assert np.max(np.abs(g[b] - g_ref)) <= 1e-4 * np.max(np.abs(g_ref))
+
+
+@pytest.mark.parametrize("nb", [1, 15, 16, 17, 127, 128, 129, 1000])
+def test_adam_sums_every_partial(nb):
+    """Partial counts around the 16 waves and the 128 loads in flight: the
+    moments against the FP64 sum.  A partial passes through at most
+    ceil(nb / 16) + 16 FP32 additions, each rounding by 2^-24 of a running
+    sum of at most sum |partial|; the products add two more."""
+    rng = np.random.default_rng(nb)
+    parts = rng.standard_normal((nb, P)).astype(np.float32)
+    w, m, v = (torch.zeros(P, dtype=torch.float32, device=DEV) for _ in range(3))
+    hpac.hpac_mlp_adam(torch.from_numpy(parts.ravel()).to(DEV), nb, w, m, v, 1e-3, 0.5, 0.5, 1e-8, 1)
+    torch.cuda.synchronize()
+    s, a = parts.astype(np.float64).sum(0), np.abs(parts.astype(np.float64)).sum(0)
+    err = (-(-nb // 16) + 16 + 2) * 2.0 ** -24 * a
+    assert np.all(np.abs(m.cpu().numpy() - 0.5 * s) <= 0.5 * err)
+    assert np.all(np.abs(v.cpu().numpy() - 0.5 * s * s) <= np.abs(s) * err + err * err)
+
+
 def inference_bound(x, w, nm):
     W1 = np.abs(oracle.bf16(w[:320])).reshape(64, 5)
     W2 = np.abs(oracle.bf16(w[384:4480])).reshape(64, 64)
