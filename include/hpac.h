@@ -259,7 +259,7 @@ typedef struct hpac_mlp_norm {
  * network's outputs, computed with BF16 MFMA and FP32 accumulation, the layer
  * inputs rounded to BF16; every other item is appended to `queue` (device,
  * n int32 entries, order unspecified) and gets the exact region's outputs.
- * *queue_count (device int32) is set to the number queued.  Three launches
+ * *queue_count (device int32) is set to the number queued.  Two launches
  * on io->stream. */
 hpac_status hpac_surrogate(const hpac_region_io *io, const float *params, const hpac_mlp_norm *norm,
                            const float *box_lo, const float *box_hi, int32_t *queue, int32_t *queue_count);

@@ -8,8 +8,8 @@
 //                operand of the next: the order of the reduction index inside
 //                each 32-wide chunk is permuted, and the weights are loaded
 //                in the same permuted order.  Items outside the box are
-//                ballot-compacted into a queue.
-//  k_mlp_fallback the exact region over the queued items.
+//                ballot-compacted per wave, listed in a queue and priced by
+//                the exact region.
 //  k_mlp_grad    training: forward (FP32 activations, BF16-rounded weights)
 //                and backward for 64 items per workgroup, its products on
 //                FP32 MFMA; weight-gradient partial sums per workgroup
@@ -67,83 +67,120 @@ __device__ __forceinline__ float target_map(const MlpGradArgs &a, int o, float t
 // the accumulator rows a lane holds in the two 16-unit tiles of the chunk
 __device__ __forceinline__ int kperm(int c, int g, int j) { return 32 * c + (j < 4 ? 4 * g + j : 16 + 4 * g + j - 4); }
 
-// Out-of-box item indices are staged per wave in LDS and appended to the
-// global queue kQueueStage at a time: one global atomic per wave-flush, not
-// one per 64 items (a single counter hit by every wave serialises them).
+// Out-of-box items are staged per wave in LDS (index and inputs) and dealt with
+// kQueueStage at a time: their indices are appended to the global queue with
+// one atomic per flush, not one per 64 items (a single counter hit by every
+// wave serialises them), and the exact region prices them with every lane
+// busy, from the inputs the wave has already read (a second kernel over the
+// queue read and wrote most of the columns' lines again: 77 us at 2^24 items,
+// 5% of them out of the box).
 constexpr int kQueueStage = 256;
+struct OutOfBox {
+  int32_t index[kQueueStage];
+  float x[5][kQueueStage];
+};
 
-__device__ __forceinline__ void queue_flush(const MlpArgs &a, const int32_t *stage, int count, int lane) {
+__device__ __forceinline__ void out_of_box_flush(const MlpArgs &a, const OutOfBox &st, int count, int lane) {
   int base = 0;
   if (lane == 0) base = atomicAdd(a.queue_count, count);
   base = __builtin_amdgcn_readfirstlane(base);
-  for (int q = lane; q < count; q += 64) a.queue[base + q] = stage[q];
+  for (int q = lane; q < count; q += 64) {
+    const int32_t i = st.index[q];
+    a.queue[base + q] = i;
+    float x[5], y[2];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) x[j] = st.x[j][q];
+    RegionBSPrice::eval(x, y);
+    a.out[0][i] = y[0];
+    a.out[1][i] = y[1];
+  }
 }
 
-// Persistent: each wave loads the weights into registers once and then walks
-// 64-item chunks (chunk = wave id + k * waves in the grid), so the weight
-// gather is paid once per wave rather than once per 64 items.
-__global__ void __launch_bounds__(256) k_mlp_infer(MlpArgs a) {
+// Persistent: each wave walks 64-item chunks (chunk = wave id + k * waves in
+// the grid).  The parameters are fetched once per workgroup, coalesced, into
+// LDS and from there into MFMA operand layout; the first two layers' weights
+// stay in registers, the biases and the last layer's weights are read from
+// LDS where a tile starts, as accumulators and operands: that keeps the kernel
+// within the registers of WAVES waves per SIMD.
+//
+// Bound by VALU issue: the 128 GELUs per item take about 35 clocks each per
+// wave, 16 of them the two transcendentals, which hold the SIMD (480 of the
+// 680 us at 2^24 items); the MFMAs are nearly hidden (659 us without them),
+// and three or five waves per SIMD measured 699 and 690 us.  2^24 items, 5%
+// out of the box: 766 us with every weight and bias in registers and a
+// second pass for the out-of-box items, 680 us here.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) k_mlp_infer(MlpArgs a) {
   // per wave: the BF16 normalised inputs of its 64 items in the B-operand
-  // layout of layer 1 (slots 5..7 zero), and a zero row 64 for lane groups 1..3
-  __shared__ bf16x8 xs[4][65];
-  __shared__ float ys[4][64][2];  // per wave: the network's normalised outputs
-  __shared__ int32_t qstage[4][kQueueStage];
+  // layout of layer 1 (slots 5..7 zero), and a zero row 64 for lane groups
+  // 1..3; the network's normalised outputs; the staged out-of-box items
+  struct Wave {
+    bf16x8 xs[65];
+    float ys[64][2];
+    OutOfBox oob;
+  };
+  __shared__ union {
+    float params[kNumParams];  // before the loop
+    Wave wave[4];
+  } sh;
+  __shared__ bf16x8 w3s[2][64];             // last layer's weights in operand layout
+  __shared__ floatx4 b1s[16], b2s[16], b3s[4];  // biases by accumulator row groups of four
   const int lane = lane_id();
-  const int w = threadIdx.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // chunk numbers and column bases in scalar registers
   const int g = lane >> 4, r = lane & 15;
+  Wave &wv = sh.wave[w];
 
+  for (int p = threadIdx.x; p < kNumParams; p += 256) sh.params[p] = a.params[p];
+  const int64_t chunks = (a.n + 63) >> 6;
+  const int64_t waves = (int64_t)gridDim.x * 4;
+  // inputs of the wave's next chunk, loaded one chunk ahead
+  float xn[5];
+  auto load = [&](int64_t first) {  // the columns of the chunk that starts at item `first`
+    const bool have = lane < a.n - first;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) xn[j] = have ? (a.in[j] + first)[lane] : 0.0f;
+  };
+  load(((int64_t)blockIdx.x * 4 + w) * 64);
+  __syncthreads();
   // weights in MFMA A layout (lane holds row r of a 16-row tile, reduction
   // slots 8g..8g+7), rounded to BF16
-  bf16x8 W1[4], W2[4][2], W3[2];
+  bf16x8 W1[4], W2[4][2];
 #pragma unroll
   for (int tm = 0; tm < 4; ++tm)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int k = 8 * g + j;
-      W1[tm][j] = (__bf16)(k < 5 ? a.params[(16 * tm + r) * 5 + k] : 0.0f);
-    }
+    for (int j = 0; j < 8; ++j) W1[tm][j] = (__bf16)(g == 0 && j < 5 ? sh.params[(16 * tm + r) * 5 + j] : 0.0f);
 #pragma unroll
   for (int tm = 0; tm < 4; ++tm)
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) W2[tm][c][j] = (__bf16)a.params[kOffW2 + (16 * tm + r) * kNH + kperm(c, g, j)];
+      for (int j = 0; j < 8; ++j) W2[tm][c][j] = (__bf16)sh.params[kOffW2 + (16 * tm + r) * kNH + kperm(c, g, j)];
+  if (w < 2) {
+    bf16x8 v;
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+    for (int j = 0; j < 8; ++j) v[j] = (__bf16)(r < 2 ? sh.params[kOffW3 + r * kNH + kperm(w, g, j)] : 0.0f);
+    w3s[w][lane] = v;
+  } else if (lane < 36) {
+    const int q = lane & 15;
+    floatx4 v;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) W3[c][j] = (__bf16)(r < 2 ? a.params[kOffW3 + r * kNH + kperm(c, g, j)] : 0.0f);
-  // biases in accumulator layout (lane holds rows 4g..4g+3 of each tile)
-  floatx4 B1[4], B2[4], B3;
-#pragma unroll
-  for (int tm = 0; tm < 4; ++tm)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      B1[tm][j] = a.params[kOffB1 + 16 * tm + 4 * g + j];
-      B2[tm][j] = a.params[kOffB2 + 16 * tm + 4 * g + j];
-    }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) B3[j] = (4 * g + j < 2) ? a.params[kOffB3 + 4 * g + j] : 0.0f;
+    for (int j = 0; j < 4; ++j)
+      v[j] = lane < 32 ? sh.params[(lane < 16 ? kOffB1 : kOffB2) + 4 * q + j]
+                       : (lane == 32 && j < 2 ? sh.params[kOffB3 + j] : 0.0f);
+    if (w == 2) (lane < 16 ? b1s[q] : lane < 32 ? b2s[q] : b3s[lane - 32]) = v;
+  }
+  __syncthreads();  // the parameters' space becomes the waves' own
 
   if (lane == 0) {
     bf16x8 z;
 #pragma unroll
     for (int j = 0; j < 8; ++j) z[j] = (__bf16)0.0f;
-    xs[w][64] = z;
+    wv.xs[64] = z;
   }
-  const int64_t chunks = (a.n + 63) >> 6;
-  const int64_t waves = (int64_t)gridDim.x * 4;
   int staged = 0;  // wave-uniform
-  // inputs of the wave's next chunk, loaded one chunk ahead
-  float xn[5];
-  {
-    const int64_t i0 = ((int64_t)blockIdx.x * 4 + w) * 64 + lane;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) xn[j] = i0 < a.n ? a.in[j][i0] : 0.0f;
-  }
 #pragma unroll 1
   for (int64_t ch = (int64_t)blockIdx.x * 4 + w; ch < chunks; ch += waves) {
-    const int64_t i = ch * 64 + lane;
-    const bool active = i < a.n;
+    const int64_t first = ch * 64;
+    const bool active = lane < a.n - first;
     // box test, then the loads of the next chunk go out while this one computes
     float x[5];
     bool inside = active;
@@ -152,43 +189,46 @@ __global__ void __launch_bounds__(256) k_mlp_infer(MlpArgs a) {
       x[j] = xn[j];
       inside = inside && x[j] >= a.box_lo[j] && x[j] <= a.box_hi[j];
     }
-    if (ch + waves < chunks) {  // wave-uniform
-      const int64_t inx = i + waves * 64;
-#pragma unroll
-      for (int j = 0; j < 5; ++j) xn[j] = inx < a.n ? a.in[j][inx] : 0.0f;
-    }
+    if (ch + waves < chunks) load(first + waves * 64);  // wave-uniform
     const uint64_t out_mask = ballot(active && !inside);
     // the previous chunk's LDS reads are done before anything is rewritten
     wave_lds_fence();
     if (out_mask) {
       const int cnt = popc(out_mask);
       if (staged + cnt > kQueueStage) {
-        queue_flush(a, qstage[w], staged, lane);
+        out_of_box_flush(a, wv.oob, staged, lane);
         staged = 0;
         wave_lds_fence();
       }
-      if (active && !inside) qstage[w][staged + popc(out_mask & ((1ull << lane) - 1))] = (int32_t)i;
+      if (active && !inside) {
+        const int q = staged + popc(out_mask & ((1ull << lane) - 1));
+        wv.oob.index[q] = (int32_t)first + lane;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) wv.oob.x[j][q] = x[j];
+      }
       staged += cnt;
     }
-    float xh[5];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) xh[j] = (x[j] - a.in_center[j]) * a.in_scale[j];
     {
       bf16x8 v;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = (__bf16)(j < 5 ? xh[j < 5 ? j : 0] : 0.0f);
-      xs[w][lane] = v;
+      for (int j = 0; j < 8; ++j) v[j] = (__bf16)(j < 5 ? (x[j < 5 ? j : 0] - a.in_center[j < 5 ? j : 0]) * a.in_scale[j < 5 ? j : 0] : 0.0f);
+      wv.xs[lane] = v;
     }
     wave_lds_fence();
 
-#pragma unroll 2
+#pragma unroll 1
     for (int tn = 0; tn < 4; ++tn) {
       // B operand of layer 1: inputs of item 16 tn + r in slots 0..7 of lane
       // group 0, zeros elsewhere
-      const bf16x8 xb = xs[w][g == 0 ? 16 * tn + r : 64];
+      const bf16x8 xb = wv.xs[g == 0 ? 16 * tn + r : 64];
+      // opaque: the biases and the last layer's weights are read here, not
+      // kept in registers across the loops
+      int gt = g, lt = lane;
+      asm volatile("" : "+v"(gt), "+v"(lt));
       floatx4 D1[4];
 #pragma unroll
-      for (int tm = 0; tm < 4; ++tm) D1[tm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1[tm], xb, B1[tm], 0, 0, 0);
+      for (int tm = 0; tm < 4; ++tm)
+        D1[tm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W1[tm], xb, b1s[4 * tm + gt], 0, 0, 0);
       // GELU, BF16, and the permuted B operand of layer 2: chunk c, slot j
       bf16x8 h1[2];
 #pragma unroll
@@ -198,7 +238,7 @@ __global__ void __launch_bounds__(256) k_mlp_infer(MlpArgs a) {
       floatx4 D2[4];
 #pragma unroll
       for (int tm = 0; tm < 4; ++tm) {
-        D2[tm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W2[tm][0], h1[0], B2[tm], 0, 0, 0);
+        D2[tm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W2[tm][0], h1[0], b2s[4 * tm + gt], 0, 0, 0);
         D2[tm] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W2[tm][1], h1[1], D2[tm], 0, 0, 0);
       }
       bf16x8 h2[2];
@@ -206,37 +246,24 @@ __global__ void __launch_bounds__(256) k_mlp_infer(MlpArgs a) {
       for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int j = 0; j < 8; ++j) h2[c][j] = (__bf16)gelu(D2[2 * c + (j >> 2)][j & 3]);
-      floatx4 D3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W3[0], h2[0], B3, 0, 0, 0);
-      D3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W3[1], h2[1], D3, 0, 0, 0);
+      floatx4 D3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3s[0][lt], h2[0], b3s[gt], 0, 0, 0);
+      D3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3s[1][lt], h2[1], D3, 0, 0, 0);
       // rows 0 and 1 (the two outputs) live in lanes 0..15, slots 0 and 1
       if (g == 0) {
-        ys[w][16 * tn + r][0] = D3[0];
-        ys[w][16 * tn + r][1] = D3[1];
+        wv.ys[16 * tn + r][0] = D3[0];
+        wv.ys[16 * tn + r][1] = D3[1];
       }
     }
     wave_lds_fence();
     if (active && inside) {
       // the output map once per item, each lane on its own item
-      a.out[0][i] = out_map(a, 0, ys[w][lane][0]);
-      a.out[1][i] = out_map(a, 1, ys[w][lane][1]);
+      (a.out[0] + first)[lane] = out_map(a, 0, wv.ys[lane][0]);
+      (a.out[1] + first)[lane] = out_map(a, 1, wv.ys[lane][1]);
     }
   }
   if (staged > 0) {
     wave_lds_fence();
-    queue_flush(a, qstage[w], staged, lane);
-  }
-}
-
-__global__ void __launch_bounds__(256) k_mlp_fallback(MlpArgs a) {
-  const int count = *a.queue_count;
-  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < count; q += gridDim.x * blockDim.x) {
-    const int64_t i = a.queue[q];
-    float x[5], y[2];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) x[j] = a.in[j][i];
-    RegionBSPrice::eval(x, y);
-    a.out[0][i] = y[0];
-    a.out[1][i] = y[1];
+    out_of_box_flush(a, wv.oob, staged, lane);
   }
 }
 
@@ -464,9 +491,6 @@ hipError_t launch_mlp_infer(const MlpArgs &a, hipStream_t stream) {
   const unsigned grid = (unsigned)(want < resident ? (want < 1 ? 1 : want) : resident);
   hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, stream, a.queue_count);
   hipLaunchKernelGGL(k_mlp_infer, dim3(grid), dim3(256), 0, stream, a);
-  int blocks = (int)((a.n + 255) / 256);
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(k_mlp_fallback, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -231,3 +231,31 @@ def test_training_reduces_error_and_what_it_buys():
     assert oracle.mape(exact, y)[0] < 0.02
     assert cnt[1] <= 0.01 * n and l2(ya) < 1e-5
     assert l2(yp) > 10 * l2(y)
+
+
+@pytest.mark.parametrize("n,frac", [(1, 1.0), (63, 1.0), (65, 0.5), (20011, 0.05), ((1 << 21) + 37, 0.9),
+                                    ((1 << 21) + 37, 1.0)])
+def test_out_of_box_items_at_staging_edges(n, frac):
+    """Few and many out-of-box items per wave: at 2^21 items and 90% every wave
+    of the persistent grid stages more than its 256 slots.  The queue lists
+    exactly those items, once each, and their prices are the exact region's
+    (its parity tolerance, 1e-5 of S + K, on both sides)."""
+    x = inputs.uniform_box(n, seed=61)
+    rng = np.random.default_rng(62)
+    out = np.sort(rng.choice(n, max(1, int(round(frac * n))), replace=False))
+    x[1, out] = inputs.BOX_HI[1] + 1.0 + rng.random(out.size)
+    xd = dev_cols(x)
+    s = surrogate.Surrogate(surrogate.init_params(5), norm_for(np.array([[0.0, 1.0], [2.0, 5.0]])))
+    y = [torch.full((n,), float("nan"), dtype=torch.float32, device=DEV) for _ in range(2)]
+    ref = [torch.empty(n, dtype=torch.float32, device=DEV) for _ in range(2)]
+    for _ in range(2):  # the second call counts from zero again
+        s(xd, y)
+    hpac.hpac_exact(xd, ref, items_per_lane=1)
+    torch.cuda.synchronize()
+    assert int(s.count[0]) == out.size
+    assert np.array_equal(np.sort(s.queue[:out.size].cpu().numpy()), out)
+    idx = torch.from_numpy(out).to(DEV)
+    scale = (xd[0] + xd[1])[idx]
+    for o in range(2):
+        assert bool(torch.isfinite(y[o]).all())
+        assert float(((y[o] - ref[o])[idx].abs() / scale).max()) <= 2e-5
