@@ -233,7 +233,7 @@ def test_training_reduces_error_and_what_it_buys():
     assert l2(yp) > 10 * l2(y)
 
 
-@pytest.mark.parametrize("n,frac", [(1, 1.0), (63, 1.0), (65, 0.5), (20011, 0.05), ((1 << 21) + 37, 0.9),
+@pytest.mark.parametrize("n,frac", [(1, 1.0), (63, 1.0), (65, 0.5), (16384, 0.3), (16385, 0.3), (20011, 0.05), ((1 << 21) + 37, 0.9),
                                     ((1 << 21) + 37, 1.0)])
 def test_out_of_box_items_at_staging_edges(n, frac):
     """Few and many out-of-box items per wave: at 2^21 items and 90% every wave
