@@ -406,8 +406,9 @@ hpac_status hpac_hydro_step_noalloc(const hpac_hydro_params *params, const hpac_
                                     const hpac_hydro_state *state, int8_t *dec_eos, int8_t *dec_hg, void *stream);
 
 /* `steps` (>= 0) timesteps with indices first_step, first_step + 1, ...:
- * the same launches as that many hpac_hydro_step calls with u and unew
- * swapped between them, issued from one host loop (no decision records).
+ * the same state as that many hpac_hydro_step calls with u and unew swapped
+ * between them, issued from one host loop (no decision records); kernels may
+ * serve two neighbouring steps, so only the state at the end is a step's.
  * On return, in stream order, the latest velocities are in state->unew if
  * `steps` is odd and in state->u if it is even. */
 hpac_status hpac_hydro_run(const hpac_hydro_params *params, const hpac_hydro_tech *tech, int32_t first_step,

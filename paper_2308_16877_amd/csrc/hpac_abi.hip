@@ -689,17 +689,7 @@ hpac_status hpac_hydro_run(const hpac_hydro_params *params, const hpac_hydro_tec
   int mode = 0, eos_mode = 0;
   const hpac_status st = hydro_prepare(fn, params, tech, first_step, state, nullptr, nullptr, &a, &mode, &eos_mode);
   if (st != HPAC_OK) return st;
-  for (int32_t k = 0; k < steps; ++k) {
-    a.step = first_step + k;
-    const hipError_t e = hpac::launch_hydro_step(a, mode, eos_mode, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_status(fn, e);
-    for (int d = 0; d < 3; ++d) {  // the new velocities are the next step's old ones
-      float *t = a.u[d];
-      a.u[d] = a.un[d];
-      a.un[d] = t;
-    }
-  }
-  return HPAC_OK;
+  return hip_status(fn, hpac::launch_hydro_run(a, mode, eos_mode, steps, (hipStream_t)stream));
 }
 
 hpac_status hpac_hydro_check(const hpac_hydro_state *state, void *stream) {

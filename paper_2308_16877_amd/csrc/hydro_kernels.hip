@@ -283,6 +283,15 @@ __device__ __forceinline__ double block_min(double v, double *red) {
   return red[0];
 }
 
+// Doubles as unsigned integers of the same order, for integer atomics.
+__device__ __forceinline__ unsigned long long ordered_key(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  return u >> 63 ? ~u : u | 0x8000000000000000ull;
+}
+__device__ __forceinline__ double key_value(unsigned long long k) {
+  return __builtin_bit_cast(double, k >> 63 ? k ^ 0x8000000000000000ull : ~k);
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ init
@@ -359,6 +368,25 @@ __device__ __forceinline__ void store_forces(float *force, int64_t E, int64_t z,
     for (int d = 0; d < 3; ++d) force[(c * 3 + d) * E + z] = f ? __builtin_fmaf(pq, B[c][d], f[c][d]) : pq * B[c][d];
 }
 
+// Volume rate sum B . u (B sums to zero, so relative to corner 0).
+__device__ __forceinline__ float volume_rate(const float (&B)[8][3], const float (&u)[8][3]) {
+  float vdot = 0.0f;
+#pragma unroll
+  for (int c = 1; c < 8; ++c)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) vdot = __builtin_fmaf(B[c][d], u[c][d] - u[0][d], vdot);
+  return vdot;
+}
+
+// The element's time-step bound in FP64.
+__device__ __forceinline__ double time_bound(const HydroArgs &a, float V, float mass, float pq, float vdot) {
+  const double Vd = (double)V, rd = (double)mass / Vd;
+  const double ceff2 = a.gamma_d * fmax((double)pq, 0.0) / rd;
+  double b = ceff2 > 0.0 ? a.cfl * cbrt(Vd) / sqrt(ceff2) : INFINITY;
+  if (vdot != 0.0f) b = fmin(b, a.dvmax * Vd / fabs((double)vdot));
+  return b;
+}
+
 template <int HG>
 __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
   __shared__ double red[256];
@@ -418,12 +446,7 @@ __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
       const float V = hex_volume<true>(x, B);
       a.vol[z] = V;
       if (!(V > 0.0f)) atomicOr(a.status, kHydroBadVolume);  // tangled (or NaN) element
-      // volume rate sum B . u (B sums to zero, so relative to corner 0)
-      float vdot = 0.0f;
-#pragma unroll
-      for (int c = 1; c < 8; ++c)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) vdot = __builtin_fmaf(B[c][d], u[c][d] - u[0][d], vdot);
+      const float vdot = volume_rate(B, u);
       if (compute_hg) {
         float f[8][3];
         hourglass(x, u, B, V, mass / V, cs, a.khg, f);
@@ -444,12 +467,7 @@ __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
       } else {
         store_forces(a.force, E, z, pq, B, nullptr);  // perforated: no hourglass force
       }
-      // time-step bound in FP64
-      const double Vd = (double)V, rd = (double)mass / Vd;
-      const double ceff2 = a.gamma_d * fmax((double)pq, 0.0) / rd;
-      double b = ceff2 > 0.0 ? a.cfl * cbrt(Vd) / sqrt(ceff2) : INFINITY;
-      if (vdot != 0.0f) b = fmin(b, a.dvmax * Vd / fabs((double)vdot));
-      bound = fmin(bound, b);
+      bound = fmin(bound, time_bound(a, V, mass, pq, vdot));
       if (kTaf && compute_hg && pushes + 1 >= a.hg_h) {  // the window is full: vote
         voted = true;
         const double th = (double)a.hg_theta;
@@ -506,7 +524,7 @@ __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
 
 // ------------------------------------------------------------------ dt
 
-__global__ void __launch_bounds__(256) k_hydro_dt(HydroArgs a, int64_t parts) {
+__global__ void __launch_bounds__(256) k_hydro_dt(HydroArgs a, int64_t parts, HydroLoop lp) {
   __shared__ double red[256];
   // sixteen independent loads per thread in flight at once: the partials
   // were just written by every XCD, so each round trip is a memory latency
@@ -523,6 +541,8 @@ __global__ void __launch_bounds__(256) k_hydro_dt(HydroArgs a, int64_t parts) {
     for (int u = 0; u < kU; ++u) m = fmin(m, v[u]);
   }
   m = block_min(m, red);
+  // every partial has been read: their space becomes a loop's slots
+  if ((int)threadIdx.x < lp.slots) lp.bounds_next[threadIdx.x] = ordered_key(INFINITY);
   if (threadIdx.x == 0) {
     const double dt = fmin(m, a.growth * a.clock[1]);
     if (!(dt > 0.0) || !isfinite(dt)) atomicOr(a.status, kHydroBadDt);
@@ -533,9 +553,21 @@ __global__ void __launch_bounds__(256) k_hydro_dt(HydroArgs a, int64_t parts) {
 
 // ------------------------------------------------------------------ nodes
 
-__global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a) {
+// kLoop: within a loop of steps there is no time-step kernel before this one;
+// every wave takes the minimum of the slots itself, and the first thread of
+// the grid keeps the clock (nobody else reads what it writes).
+template <bool kLoop>
+__global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a, HydroLoop lp) {
   const int64_t v = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (v >= a.Nn) return;
+  unsigned long long key = ~0ull;
+  double prev = 0.0;
+  if (kLoop) {
+    const int lane = lane_id();
+    if (lane < lp.slots) key = lp.bounds[lane];
+    prev = *lp.dt_prev;
+  } else if (v >= a.Nn) {
+    return;
+  }
   const int n = a.n;
   const int64_t m = n + 1, E = a.E;
   const uint32_t t = a.dm.quo((uint32_t)v), kk = a.dm.quo(t);
@@ -547,7 +579,7 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a) {
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
     int64_t ei = i - (c & 1), ej = j - ((c >> 1) & 1), ek = k - ((c >> 2) & 1);
-    in[c] = ei >= 0 && ej >= 0 && ek >= 0 && ei < n && ej < n && ek < n;
+    in[c] = ei >= 0 && ej >= 0 && ek >= 0 && ei < n && ej < n && ek < n;  // a thread past the last node has k > n
     ei = ei < 0 ? 0 : ei < n ? ei : n - 1;
     ej = ej < 0 ? 0 : ej < n ? ej : n - 1;
     ek = ek < 0 ? 0 : ek < n ? ek : n - 1;
@@ -555,13 +587,35 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) f[c][d] = a.force[(c * 3 + d) * E + z];
   }
+  const int64_t vl = v < a.Nn ? v : a.Nn - 1;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    u0[d] = a.u[d][v];
-    x0[d] = a.x[d][v];
+    u0[d] = a.u[d][vl];
+    x0[d] = a.x[d][vl];
   }
-  const float dt = (float)a.clock[1];
-  const float inv_m = 1.0f / a.mnode[v];
+  const float mn = a.mnode[vl];
+  double dtd;
+  if (kLoop) {
+#pragma unroll
+    for (int m2 = 1; m2 < 64; m2 <<= 1) {
+      const unsigned long long o = __shfl_xor(key, m2, 64);
+      key = o < key ? o : key;
+    }
+    dtd = fmin(key_value(key), a.growth * prev);
+    if (blockIdx.x == 0) {
+      if ((int)threadIdx.x < lp.slots) lp.bounds_next[threadIdx.x] = ordered_key(INFINITY);
+      if (threadIdx.x == 0) {
+        if (!(dtd > 0.0) || !isfinite(dtd)) atomicOr(a.status, kHydroBadDt);
+        a.clock[0] += dtd;
+        *lp.dt = dtd;
+      }
+    }
+    if (v >= a.Nn) return;
+  } else {
+    dtd = a.clock[1];
+  }
+  const float dt = (float)dtd;
+  const float inv_m = 1.0f / mn;
   float F[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int c = 0; c < 8; ++c)
@@ -579,19 +633,33 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a) {
 
 // ------------------------------------------------------------------ EOS
 
-template <int EOS>
-__global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a) {
-  constexpr bool kTaf = EOS != kEosExact;
+// NEXT (within a loop of steps): the next step's forces, kHgExact or kHgNone,
+// follow in the same kernel.  Both sides are functions of the element's new
+// positions and velocities, so the gathers, the volume and its gradient are
+// formed once, and pressure, viscosity and sound speed stay in registers; the
+// next step's time-step bound goes to one of lp.slots minima by an integer
+// atomic.  kNoNext: the EOS alone.  Fused, the kernel holds 200 registers (two
+// waves per SIMD; held to three it spills and takes 60 us instead of 37 at
+// 90^3): a step on 90^3 elements takes 54 us instead of 66 in four launches
+// (force 23.0, time step 4.7, node 16.2, EOS 21.5), on 24^3 with EOS TAF 11.8
+// instead of 18.3.
+template <int EOS, int NEXT>
+__global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a, HydroLoop lp) {
+  constexpr bool kTaf = EOS != kEosExact, kFused = NEXT != kNoNext;
+  static_assert(!kFused || EOS != kEosTafBlock, "block level steps one kernel at a time");
   const int n = a.n;
   const int64_t E = a.E;
   const int64_t blk = xcd_block(blockIdx.x, gridDim.x);  // element block: the block-level group
   const int64_t z = blk * blockDim.x + threadIdx.x;
   const int64_t w = z >> 6;
-  // whole waves past the last element leave, except at block level, where
-  // every lane of the workgroup must reach its barriers
-  if (EOS != kEosTafBlock && w >= a.W) return;
+  // whole waves past the last element leave, except where every lane of the
+  // workgroup must reach barriers
+  if (EOS != kEosTafBlock && !kFused && w >= a.W) return;
   const int lane = lane_id();
   const bool active = z < E;
+  // the end of a loop: the last step's time step goes where single steps keep it
+  if (!kFused && z == 0 && lp.dt != &a.clock[1]) a.clock[1] = *lp.dt;
+  bool approx = false;  // the element keeps its EOS outputs
   int pushes = 0;
   __shared__ int tally[3];  // block level: active elements, votes to approximate, waves that voted
   if (EOS == kEosTafBlock) {
@@ -607,83 +675,121 @@ __global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a) {
     if (threadIdx.x < 3) tally[threadIdx.x] = 0;
     __syncthreads();
   }
-  if (EOS == kEosTafWave) {
+  if (EOS == kEosTafWave && (!kFused || w < a.W)) {
     const int rho = a.rho_eos[w];
     if (rho > 0) {
       if (lane == 0) {
         a.rho_eos[w] = rho - 1;
         if (a.dec_eos) a.dec_eos[w] = 1;
       }
-      return;
+      approx = true;
+      if (!kFused) return;
     }
     pushes = a.z_eos[w];
   }
   if (EOS == kEosTafThread) {
-    if (!active) return;
-    const int rho = a.rho_eos[z];
-    if (rho > 0) {
-      a.rho_eos[z] = rho - 1;
-      if (a.dec_eos) a.dec_eos[z] = 1;
-      return;
+    if (!kFused && !active) return;
+    if (active) {
+      const int rho = a.rho_eos[z];
+      if (rho > 0) {
+        a.rho_eos[z] = rho - 1;
+        if (a.dec_eos) a.dec_eos[z] = 1;
+        approx = true;
+        if (!kFused) return;
+      }
+      pushes = a.z_eos[z];
     }
-    pushes = a.z_eos[z];
   }
   bool crit = false, voted = false;
+  double bound = INFINITY;
   if (active) {
     const ElemIdx ei(z, a.dn);
-    float x[8][3], u0[8][3], u1[8][3], B[8][3];
+    float x[8][3], u1[8][3], B[8][3];
     // every load before the atomic and the stores, as in the force kernel
     gather3(a.x, ei, n, x);
-    gather3(a.u, ei, n, u0);
     gather3(a.un, ei, n, u1);
-    const float dt = (float)a.clock[1], m = a.mass[z], e0 = a.e[z], c0 = a.c[z];
-    float W = 0.0f;
+    const float m = a.mass[z];
+    float p1 = 0.0f, q1 = 0.0f, c1 = 0.0f;
+    if (kFused && approx) {
+      p1 = a.p[z];
+      q1 = a.q[z];
+      c1 = a.c[z];
+    }
+    float V1;
+    if (!kTaf || !approx) {
+      float u0[8][3];
+      gather3(a.u, ei, n, u0);
+      const float dt = (float)*lp.dt, e0 = a.e[z], c0 = a.c[z];
+      float W = 0.0f;
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
+      for (int c = 0; c < 8; ++c)
 #pragma unroll
-      for (int d = 0; d < 3; ++d) W = __builtin_fmaf(a.force[(c * 3 + d) * E + z], 0.5f * (u0[c][d] + u1[c][d]), W);
-    const float V1 = hex_volume<true>(x, B);
-    if (!(V1 > 0.0f)) atomicOr(a.status, kHydroBadVolume);
-    // volume rate sum B . u (B sums to zero, so relative to corner 0)
-    float vdot = 0.0f;
+        for (int d = 0; d < 3; ++d) W = __builtin_fmaf(a.force[(c * 3 + d) * E + z], 0.5f * (u0[c][d] + u1[c][d]), W);
+      // the work, the volume and its rate one after the other: interleaved, they
+      // hold more in registers at once and measured 1.4% slower per step
+      __builtin_amdgcn_sched_barrier(0);
+      V1 = hex_volume<true>(x, B);
+      if (!(V1 > 0.0f)) atomicOr(a.status, kHydroBadVolume);
+      __builtin_amdgcn_sched_barrier(0);
+      // volume rate sum B . u (B sums to zero, so relative to corner 0)
+      float vdot = 0.0f;
 #pragma unroll
-    for (int c = 1; c < 8; ++c)
+      for (int c = 1; c < 8; ++c)
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        vdot = __builtin_fmaf(B[c][d], 0.5f * (u0[c][d] + u1[c][d]) - 0.5f * (u0[0][d] + u1[0][d]), vdot);
-    const float e1 = e0 - dt * W / m;
-    const float rho1 = m / V1;
-    const float cv = cbrtf(V1);
-    const float du = vdot / (cv * cv);
-    const float q1 = du < 0.0f ? rho1 * (a.cq * du * du + a.cl * c0 * fabsf(du)) : 0.0f;
-    const float p1 = (a.gamma - 1.0f) * rho1 * e1;
-    const float c1 = sqrtf(a.gamma * fmaxf(p1, 0.0f) / rho1);
-    a.e[z] = e1;
-    a.p[z] = p1;
-    a.q[z] = q1;
-    a.c[z] = c1;
-    if (kTaf) {
-      const int slot = pushes % a.eos_h;
-      const float y[4] = {e1, p1, q1, c1};
-#pragma unroll
-      for (int o = 0; o < 4; ++o) a.weos[((int64_t)slot * 4 + o) * E + z] = y[o];
-      if (pushes + 1 >= a.eos_h) {
-        voted = true;
-        const double th = (double)a.eos_theta;
-        crit = window_rsd_below<4, 4>(a.weos, E, z, a.eos_h, slot, th * th, th > 0.0);
+        for (int d = 0; d < 3; ++d)
+          vdot = __builtin_fmaf(B[c][d], 0.5f * (u0[c][d] + u1[c][d]) - 0.5f * (u0[0][d] + u1[0][d]), vdot);
+      const float e1 = e0 - dt * W / m;
+      const float rho1 = m / V1;
+      const float cv = cbrtf(V1);
+      const float du = vdot / (cv * cv);
+      q1 = du < 0.0f ? rho1 * (a.cq * du * du + a.cl * c0 * fabsf(du)) : 0.0f;
+      p1 = (a.gamma - 1.0f) * rho1 * e1;
+      c1 = sqrtf(a.gamma * fmaxf(p1, 0.0f) / rho1);
+      a.e[z] = e1;
+      if (!kFused || kTaf) {  // else the loop's last EOS writes them
+        a.p[z] = p1;
+        a.q[z] = q1;
       }
+      a.c[z] = c1;
+      if (kTaf) {
+        const int slot = pushes % a.eos_h;
+        const float y[4] = {e1, p1, q1, c1};
+#pragma unroll
+        for (int o = 0; o < 4; ++o) a.weos[((int64_t)slot * 4 + o) * E + z] = y[o];
+        if (pushes + 1 >= a.eos_h) {
+          voted = true;
+          const double th = (double)a.eos_theta;
+          crit = window_rsd_below<4, 4>(a.weos, E, z, a.eos_h, slot, th * th, th > 0.0);
+        }
+      }
+    } else {
+      V1 = hex_volume<true>(x, B);
+      if (!(V1 > 0.0f)) atomicOr(a.status, kHydroBadVolume);
+    }
+    if (kFused) {
+      if (lp.store_vol) a.vol[z] = V1;
+      const float pq = p1 + q1;
+      const float vdot = volume_rate(B, u1);
+      if (NEXT == kHgExact) {
+        float f[8][3];
+        hourglass(x, u1, B, V1, m / V1, c1, a.khg, f);
+        store_forces(a.force, E, z, pq, B, f);
+      } else {
+        store_forces(a.force, E, z, pq, B, nullptr);
+      }
+      bound = fmin(bound, time_bound(a, V1, m, pq, vdot));
     }
   }
-  if (EOS == kEosTafThread) {
+  if (EOS == kEosTafThread && active && !approx) {
     a.z_eos[z] = pushes + 1;
     if (crit) a.rho_eos[z] = a.eos_p;
     if (a.dec_eos) a.dec_eos[z] = 0;
   }
-  if (EOS == kEosTafWave) {
+  if (EOS == kEosTafWave && !approx) {
     const uint64_t amask = ballot(active);
     const uint64_t vmask = ballot(crit);
     const bool any_vote = ballot(voted) != 0;
-    if (lane == 0) {
+    if (lane == 0 && w < a.W) {
       a.z_eos[w] = pushes + 1;
       if (any_vote && majority(popc(vmask), popc(amask))) a.rho_eos[w] = a.eos_p;
       if (a.dec_eos) a.dec_eos[w] = 0;
@@ -704,6 +810,15 @@ __global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a) {
       if (tally[2] > 0 && majority(tally[1], tally[0])) a.rho_eos[blk] = a.eos_p;
       if (a.dec_eos) a.dec_eos[blk] = 0;
     }
+  }
+  if (kFused) {
+    __shared__ double mins[4];
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) bound = fmin(bound, __shfl_xor(bound, s, 64));
+    if (lane == 0) mins[threadIdx.x >> 6] = bound;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      atomicMin(&lp.bounds[blockIdx.x % lp.slots], ordered_key(fmin(fmin(mins[0], mins[1]), fmin(mins[2], mins[3]))));
   }
 }
 
@@ -755,31 +870,112 @@ hipError_t launch_hydro_init(const HydroArgs &a, double e_origin, double dt0, hi
   return hipGetLastError();
 }
 
-hipError_t launch_hydro_step(const HydroArgs &a, int hg_mode, int eos_mode, hipStream_t s) {
-  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256);
+// The force mode of step a.step: with one item per lane the herded rule keeps
+// or drops the whole step.
+static int step_hg_mode(const HydroArgs &a, int hg_mode) {
   if (hg_mode == kHgPerfo && a.hg_ipt == 1 && a.perfo_param > 0 && (a.perfo_kind == 0 || a.perfo_kind == 1)) {
-    // one item per lane: the herded rule keeps or drops the whole step
     const int r = (int)((int64_t)a.step % a.perfo_param);
     const bool keep = a.perfo_kind == 0 ? r != a.perfo_param - 1 : r == 0;
-    hg_mode = keep ? kHgExact : kHgNone;
+    return keep ? kHgExact : kHgNone;
   }
+  return hg_mode;
+}
+
+static void go_force(const HydroArgs &a, int hg_mode, unsigned blocks, hipStream_t s) {
   switch (hg_mode) {
-    case kHgExact: hipLaunchKernelGGL(k_hydro_force<kHgExact>, dim3(fblocks), dim3(256), 0, s, a); break;
-    case kHgTafWave: hipLaunchKernelGGL(k_hydro_force<kHgTafWave>, dim3(fblocks), dim3(256), 0, s, a); break;
-    case kHgTafThread: hipLaunchKernelGGL(k_hydro_force<kHgTafThread>, dim3(fblocks), dim3(256), 0, s, a); break;
-    case kHgTafBlock: hipLaunchKernelGGL(k_hydro_force<kHgTafBlock>, dim3(fblocks), dim3(256), 0, s, a); break;
-    case kHgNone: hipLaunchKernelGGL(k_hydro_force<kHgNone>, dim3(fblocks), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL(k_hydro_force<kHgPerfo>, dim3(fblocks), dim3(256), 0, s, a); break;
+    case kHgExact: hipLaunchKernelGGL(k_hydro_force<kHgExact>, dim3(blocks), dim3(256), 0, s, a); break;
+    case kHgTafWave: hipLaunchKernelGGL(k_hydro_force<kHgTafWave>, dim3(blocks), dim3(256), 0, s, a); break;
+    case kHgTafThread: hipLaunchKernelGGL(k_hydro_force<kHgTafThread>, dim3(blocks), dim3(256), 0, s, a); break;
+    case kHgTafBlock: hipLaunchKernelGGL(k_hydro_force<kHgTafBlock>, dim3(blocks), dim3(256), 0, s, a); break;
+    case kHgNone: hipLaunchKernelGGL(k_hydro_force<kHgNone>, dim3(blocks), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL(k_hydro_force<kHgPerfo>, dim3(blocks), dim3(256), 0, s, a); break;
   }
-  hipLaunchKernelGGL(k_hydro_dt, dim3(1), dim3(256), 0, s, a, (int64_t)fblocks);
-  hipLaunchKernelGGL(k_hydro_node, dim3((unsigned)((a.Nn + 255) / 256)), dim3(256), 0, s, a);
-  const unsigned eblocks = (unsigned)((hydro_lanes(a.E, 1) + 255) / 256);
+}
+
+template <int NEXT>
+static void go_eos(const HydroArgs &a, const HydroLoop &lp, int eos_mode, hipStream_t s) {
+  const dim3 g((unsigned)((hydro_lanes(a.E, 1) + 255) / 256)), b(256);
   switch (eos_mode) {
-    case kEosExact: hipLaunchKernelGGL(k_hydro_eos<kEosExact>, dim3(eblocks), dim3(256), 0, s, a); break;
-    case kEosTafWave: hipLaunchKernelGGL(k_hydro_eos<kEosTafWave>, dim3(eblocks), dim3(256), 0, s, a); break;
-    case kEosTafThread: hipLaunchKernelGGL(k_hydro_eos<kEosTafThread>, dim3(eblocks), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL(k_hydro_eos<kEosTafBlock>, dim3(eblocks), dim3(256), 0, s, a); break;
+    case kEosExact: hipLaunchKernelGGL((k_hydro_eos<kEosExact, NEXT>), g, b, 0, s, a, lp); break;
+    case kEosTafWave: hipLaunchKernelGGL((k_hydro_eos<kEosTafWave, NEXT>), g, b, 0, s, a, lp); break;
+    case kEosTafThread: hipLaunchKernelGGL((k_hydro_eos<kEosTafThread, NEXT>), g, b, 0, s, a, lp); break;
+    default:
+      if constexpr (NEXT == kNoNext) hipLaunchKernelGGL((k_hydro_eos<kEosTafBlock, NEXT>), g, b, 0, s, a, lp);
+      break;
   }
+}
+
+hipError_t launch_hydro_step(const HydroArgs &a, int hg_mode, int eos_mode, hipStream_t s) {
+  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256), nblocks = (unsigned)((a.Nn + 255) / 256);
+  HydroLoop lp = {};
+  lp.dt = &a.clock[1];
+  go_force(a, step_hg_mode(a, hg_mode), fblocks, s);
+  hipLaunchKernelGGL(k_hydro_dt, dim3(1), dim3(256), 0, s, a, (int64_t)fblocks, lp);
+  hipLaunchKernelGGL(k_hydro_node<false>, dim3(nblocks), dim3(256), 0, s, a, lp);
+  go_eos<kNoNext>(a, lp, eos_mode, s);
+  return hipGetLastError();
+}
+
+// A loop of steps.  Where the EOS and the next step's forces can share a
+// kernel (no hourglass TAF, no perforation within a step, EOS decisions of a
+// thread or wave), a step is two launches instead of four: the node kernel,
+// which also forms the time step, and the EOS with the next step's forces.
+// The time-step bounds live in the caller's partial array: two sets of `slots`
+// minima, used by steps in turn (the node kernel that reads one clears the
+// other), and the time steps of odd steps; even ones are in clock[1].
+// Same values as single steps.
+hipError_t launch_hydro_run(HydroArgs a, int hg_mode, int eos_mode, int steps, hipStream_t s) {
+  const int64_t parts = hydro_partials(a.E);
+  const bool whole = hg_mode == kHgExact || step_hg_mode(a, hg_mode) != kHgPerfo;
+  const bool fused = steps > 1 && parts >= 3 && eos_mode != kEosTafBlock && whole && hg_mode != kHgTafWave &&
+                     hg_mode != kHgTafThread && hg_mode != kHgTafBlock;
+  auto swap_u = [&] {  // the new velocities are the next step's old ones
+    for (int d = 0; d < 3; ++d) {
+      float *t = a.u[d];
+      a.u[d] = a.un[d];
+      a.un[d] = t;
+    }
+  };
+  if (!fused) {
+    for (int k = 0; k < steps; ++k) {
+      const hipError_t e = launch_hydro_step(a, hg_mode, eos_mode, s);
+      if (e != hipSuccess) return e;
+      a.step += 1;
+      swap_u();
+    }
+    return hipSuccess;
+  }
+  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256), nblocks = (unsigned)((a.Nn + 255) / 256);
+  const int slots = (int)((parts - 1) / 2 < 64 ? (parts - 1) / 2 : 64);
+  unsigned long long *const set[2] = {(unsigned long long *)a.dt_partials, (unsigned long long *)a.dt_partials + slots};
+  double *const cell[2] = {&a.clock[1], a.dt_partials + 2 * slots};
+  HydroLoop lp = {};
+  lp.slots = slots;
+  lp.dt = cell[0];
+  lp.bounds_next = set[1];
+  go_force(a, step_hg_mode(a, hg_mode), fblocks, s);
+  hipLaunchKernelGGL(k_hydro_dt, dim3(1), dim3(256), 0, s, a, (int64_t)fblocks, lp);
+  hipLaunchKernelGGL(k_hydro_node<false>, dim3(nblocks), dim3(256), 0, s, a, lp);
+  for (int k = 0; k + 1 < steps; ++k) {
+    // step k's EOS and step k + 1's forces
+    lp.dt = cell[k & 1];
+    lp.bounds = set[(k + 1) & 1];
+    lp.store_vol = k + 2 == steps;
+    a.step += 1;
+    if (step_hg_mode(a, hg_mode) == kHgNone)
+      go_eos<kHgNone>(a, lp, eos_mode, s);
+    else
+      go_eos<kHgExact>(a, lp, eos_mode, s);
+    swap_u();
+    // step k + 1's nodes
+    lp.dt_prev = cell[k & 1];
+    lp.dt = cell[(k + 1) & 1];
+    lp.bounds_next = set[k & 1];
+    hipLaunchKernelGGL(k_hydro_node<true>, dim3(nblocks), dim3(256), 0, s, a, lp);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  go_eos<kNoNext>(a, lp, eos_mode, s);
   return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@ namespace hpac {
 // hourglass force, a step that herded perforation drops as a whole):
 constexpr int kHgExact = 0, kHgTafWave = 1, kHgTafThread = 2, kHgPerfo = 3, kHgNone = 4, kHgTafBlock = 5;
 constexpr int kEosExact = 0, kEosTafWave = 1, kEosTafThread = 2, kEosTafBlock = 3;
+constexpr int kNoNext = -1;  // an EOS kernel without the next step's forces
 constexpr int kHydroBlock = 256;  // elements of a workgroup, the block-level decision group
 
 // Division by a fixed divisor d >= 1 of dividends below 2^31 as one 64-bit
@@ -60,6 +61,15 @@ struct HydroArgs {
   int64_t hg_L;    // its logical lanes
   int32_t step;    // timestep index (perforation offset)
 };
+// What the kernels of a loop of steps hand each other (single steps: dt only).
+struct HydroLoop {
+  double *dt;                       // the step's time step (single steps: clock[1])
+  const double *dt_prev;            // the step before's
+  unsigned long long *bounds;       // slots of the current step's bounds, ordered keys
+  unsigned long long *bounds_next;  // slots to clear for the next step's
+  int slots;                        // 0: no slots
+  int store_vol;                    // the fused kernel stores the element volumes
+};
 constexpr int32_t kHydroBadVolume = 1, kHydroBadDt = 2;
 int64_t hydro_lanes(int64_t E, int ipt);
 int64_t hydro_partials(int64_t E);
@@ -71,5 +81,6 @@ constexpr int64_t kHydroScratchPartials = 65536;
 hipError_t hydro_scratch(hipStream_t stream, double **ptr);
 hipError_t launch_hydro_init(const HydroArgs &a, double e_origin, double dt0, hipStream_t stream);
 hipError_t launch_hydro_step(const HydroArgs &a, int hg_mode, int eos_mode, hipStream_t stream);
+hipError_t launch_hydro_run(HydroArgs a, int hg_mode, int eos_mode, int steps, hipStream_t stream);
 
 }  // namespace hpac

@@ -438,3 +438,27 @@ def test_whole_run_qoi_error_matches_oracle(name, tech):
         eg, eo = abs(qg[name] / qg["exact"] - 1), abs(qo[name] / qo["exact"] - 1)
         say("%s n=%d: QoI error GPU %.3e oracle %.3e" % (name, n, eg, eo))
         assert abs(eg - eo) <= 1e-4
+
+
+@pytest.mark.parametrize("n", [8, 9, 11, 33, 41])
+@pytest.mark.parametrize("tech", [
+    Tech(), Tech(eos=(2, 2, 0.01, "thread")), Tech(eos=(2, 3, 0.01, "wave")), Tech(perfo=("large", 3, 1)),
+    Tech(eos=(3, 2, 0.01, "thread"), perfo=("small", 2, 1)),
+], ids=["exact", "eos_thread", "eos_wave", "perfo_large", "eos_thread_perfo"])
+def test_loop_of_steps_equals_single_steps_at_slot_edges(n, tech):
+    """The loop shares kernels between steps where a mesh has at least three
+    workgroups of elements (9^3 is the smallest), with 1, 2, 64 (41^3: 270
+    workgroups) and in between (33^3: 64 of at most 70) slots for the
+    time-step bounds, ragged last workgroups among them: loops of 1 to 4 steps
+    leave every field as single steps do, bit for bit."""
+    a, b = Hydro(n, tech=tech), Hydro(n, tech=tech)
+    for k in (1, 2, 3, 4, 2):
+        a.run(k)
+        for _ in range(k):
+            b.step()
+        torch.cuda.synchronize()
+        ga, gb = a.numpy_state(), b.numpy_state()
+        for f, va in ga.items():
+            if va is not None:
+                assert np.array_equal(va, gb[f]), (k, f)
+    assert int(a.status.item()) == 0
