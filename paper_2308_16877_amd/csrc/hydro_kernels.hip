@@ -33,14 +33,14 @@
 //
 // The kernels are bound by memory, by its latency on small meshes: every
 // kernel issues all of its loads before it waits for the first and before its
-// first store.  With the node gather's corners loaded one branch after the
-// other, and loads behind stores, a step took 20.2 us on 24^3 elements (node
-// kernel 6.9 us, now 4.0) and 67.4 on 90^3 (force 24.0, node 17.0 us, now
-// 23.0 and 16.2); now 17.0 and 66.2.
+// first store (with the node gather's corners loaded one branch after the
+// other the node kernel took 6.9 us on 24^3 elements, now 4.0, and 17.0 on
+// 90^3, now 16.2).
 #include "launch_hydro.hpp"
 #include "wave.hpp"
 
 #include <mutex>
+#include <type_traits>
 
 namespace hpac {
 
@@ -193,28 +193,57 @@ __device__ __forceinline__ void hourglass(const float (&x)[8][3], const float (&
     }
 }
 
-struct ElemIdx {
-  int64_t z;
-  int64_t node0;  // node of corner 0
-  __device__ ElemIdx(int64_t z_, const DivBy &dn) : z(z_) {
-    const int64_t n = dn.d, m = n + 1;
-    const uint32_t t = dn.quo((uint32_t)z_), k = dn.quo(t);
-    const int64_t i = z_ - (int64_t)t * n, j = (int64_t)t - (int64_t)k * n;
-    node0 = i + m * (j + m * k);
-  }
-  __device__ int64_t node(int c, int n) const {
-    const int64_t m = n + 1;
-    return node0 + (c & 1) + m * (((c >> 1) & 1) + m * ((c >> 2) & 1));
+// Element and node arrays hold at most 1001^3 floats, so a byte offset into
+// one fits 32 bits: a load or store takes the array's base from scalar
+// registers and one 32-bit offset, the same for every array of its kind,
+// instead of a 64-bit address formed per access.  The fused kernel goes from
+// 200 to 161 registers (three waves per SIMD instead of two) and from 37.4 to
+// 30.4 us at 90^3, the EOS alone from 22.5 to 18.6, the force from 23.0 to 21.2.
+template <class T>
+__device__ __forceinline__ T &at(T *base, uint32_t off) {
+  using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return *(T *)((Byte *)base + (uint64_t)off);
+}
+
+// The 24 planes of the corner forces in order: the current plane's base in
+// scalar registers, opaque so that the planes' bases are not all formed (and
+// held, in vector registers too) beforehand.
+template <class T>
+struct Planes {
+  T *base;
+  uint64_t off = 0;
+  __device__ __forceinline__ T *next(int64_t E) {
+    using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+    T *p = (T *)((Byte *)base + off);
+    off += 4 * (uint64_t)E;
+    asm volatile("" : "+s"(off));
+    return p;
   }
 };
 
-__device__ __forceinline__ void gather3(const float *const *src, const ElemIdx &e, int n, float (&v)[8][3]) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const int64_t nd = e.node(c, n);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) v[c][d] = src[d][nd];
+struct ElemIdx {
+  uint32_t z;        // byte offset of the element
+  uint32_t node[4];  // byte offsets of the nodes of corners 0, 2, 4 and 6; the odd ones follow them
+  __device__ ElemIdx(int64_t z_, const DivBy &dn) {
+    const uint32_t n = dn.d, m = n + 1, ze = (uint32_t)z_;
+    const uint32_t t = dn.quo(ze), k = dn.quo(t);
+    const uint32_t i = ze - t * n, j = t - k * n;
+    z = 4 * ze;
+    node[0] = 4 * (i + m * (j + m * k));
+    node[1] = node[0] + 4 * m;
+    node[2] = node[0] + 4 * m * m;
+    node[3] = node[2] + 4 * m;
   }
+};
+
+// The second of two neighbouring nodes is a load of its own: its offset is a
+// 32-bit sum, which the compiler cannot merge into one 8-byte load at a
+// 4-byte-aligned address (merged, the fused kernel took 33.5 us).
+__device__ __forceinline__ void gather3(const float *const *src, const ElemIdx &e, float (&v)[8][3]) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) v[c][d] = at(src[d], e.node[c >> 1] + (c & 1 ? 4u : 0u));
 }
 
 // Whether the RSD of every output over the h window slots is below theta.
@@ -360,12 +389,14 @@ __global__ void __launch_bounds__(256) k_hydro_init_groups(HydroArgs a, double d
 // ------------------------------------------------------------------ force
 
 // Corner forces (p + q) B + f of one element, f = NULL for none.
-__device__ __forceinline__ void store_forces(float *force, int64_t E, int64_t z, float pq, const float (&B)[8][3],
-                                             const float (*f)[3]) {
+__device__ __forceinline__ void store_forces(float *force, int64_t E, const ElemIdx &ei, float pq,
+                                             const float (&B)[8][3], const float (*f)[3]) {
+  Planes<float> plane{force};
 #pragma unroll
   for (int c = 0; c < 8; ++c)
 #pragma unroll
-    for (int d = 0; d < 3; ++d) force[(c * 3 + d) * E + z] = f ? __builtin_fmaf(pq, B[c][d], f[c][d]) : pq * B[c][d];
+    for (int d = 0; d < 3; ++d)
+      at(plane.next(E), ei.z) = f ? __builtin_fmaf(pq, B[c][d], f[c][d]) : pq * B[c][d];
 }
 
 // Volume rate sum B . u (B sums to zero, so relative to corner 0).
@@ -390,7 +421,6 @@ __device__ __forceinline__ double time_bound(const HydroArgs &a, float V, float 
 template <int HG>
 __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
   __shared__ double red[256];
-  const int n = a.n;
   const int64_t E = a.E;
   const int64_t blk = xcd_block(blockIdx.x, gridDim.x);  // element block: the block-level group
   const int64_t l = blk * blockDim.x + threadIdx.x;
@@ -440,17 +470,17 @@ __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
       float x[8][3], u[8][3], B[8][3];
       // every load before the first store: a store could alias a later load,
       // which would then wait for a memory latency of its own
-      gather3(a.x, ei, n, x);
-      gather3(a.u, ei, n, u);
-      const float pq = a.p[z] + a.q[z], mass = a.mass[z], cs = a.c[z];
+      gather3(a.x, ei, x);
+      gather3(a.u, ei, u);
+      const float pq = at(a.p, ei.z) + at(a.q, ei.z), mass = at(a.mass, ei.z), cs = at(a.c, ei.z);
       const float V = hex_volume<true>(x, B);
-      a.vol[z] = V;
+      at(a.vol, ei.z) = V;
       if (!(V > 0.0f)) atomicOr(a.status, kHydroBadVolume);  // tangled (or NaN) element
       const float vdot = volume_rate(B, u);
       if (compute_hg) {
         float f[8][3];
         hourglass(x, u, B, V, mass / V, cs, a.khg, f);
-        store_forces(a.force, E, z, pq, B, f);
+        store_forces(a.force, E, ei, pq, B, f);
         if (kTaf) {  // push the accurate forces
           const int slot = pushes % a.hg_h;
 #pragma unroll
@@ -463,9 +493,9 @@ __global__ void __launch_bounds__(256) k_hydro_force(HydroArgs a) {
         float f[8][3];
 #pragma unroll
         for (int o = 0; o < 24; ++o) f[o / 3][o % 3] = a.whg[((int64_t)slot * 24 + o) * E + z];
-        store_forces(a.force, E, z, pq, B, f);
+        store_forces(a.force, E, ei, pq, B, f);
       } else {
-        store_forces(a.force, E, z, pq, B, nullptr);  // perforated: no hourglass force
+        store_forces(a.force, E, ei, pq, B, nullptr);  // perforated: no hourglass force
       }
       bound = fmin(bound, time_bound(a, V, mass, pq, vdot));
       if (kTaf && compute_hg && pushes + 1 >= a.hg_h) {  // the window is full: vote
@@ -568,32 +598,38 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a, HydroLoop lp) {
   } else if (v >= a.Nn) {
     return;
   }
-  const int n = a.n;
-  const int64_t m = n + 1, E = a.E;
+  const int n = a.n, m = n + 1;
+  const int64_t E = a.E;
   const uint32_t t = a.dm.quo((uint32_t)v), kk = a.dm.quo(t);
-  const int64_t i = v - (int64_t)t * m, j = (int64_t)t - (int64_t)kk * m, k = kk;
+  const int i = (int)((uint32_t)v - t * m), j = (int)(t - kk * m), k = (int)kk;
   // every load is issued at once, a corner outside the mesh reading the element
   // next to it instead (a load per branch would wait for eight latencies in turn)
   float f[8][3], u0[3], x0[3];
   bool in[8];
+  uint32_t zx[2], zy[2], zz[2];  // byte offsets of the two adjacent elements of each direction
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    auto clip = [&](int q) { return (uint32_t)(q < 0 ? 0 : q < n ? q : n - 1); };
+    zx[s] = 4 * clip(i - s);
+    zy[s] = 4 * clip(j - s) * (uint32_t)n;
+    zz[s] = 4 * clip(k - s) * (uint32_t)n * (uint32_t)n;
+  }
+  Planes<const float> plane{a.force};
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
-    int64_t ei = i - (c & 1), ej = j - ((c >> 1) & 1), ek = k - ((c >> 2) & 1);
+    const int ei = i - (c & 1), ej = j - ((c >> 1) & 1), ek = k - ((c >> 2) & 1);
     in[c] = ei >= 0 && ej >= 0 && ek >= 0 && ei < n && ej < n && ek < n;  // a thread past the last node has k > n
-    ei = ei < 0 ? 0 : ei < n ? ei : n - 1;
-    ej = ej < 0 ? 0 : ej < n ? ej : n - 1;
-    ek = ek < 0 ? 0 : ek < n ? ek : n - 1;
-    const int64_t z = ei + n * (ej + (int64_t)n * ek);
+    const uint32_t z = zx[c & 1] + zy[(c >> 1) & 1] + zz[(c >> 2) & 1];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) f[c][d] = a.force[(c * 3 + d) * E + z];
+    for (int d = 0; d < 3; ++d) f[c][d] = at(plane.next(E), z);
   }
-  const int64_t vl = v < a.Nn ? v : a.Nn - 1;
+  const uint32_t vl = 4 * (uint32_t)(v < a.Nn ? v : a.Nn - 1);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    u0[d] = a.u[d][vl];
-    x0[d] = a.x[d][vl];
+    u0[d] = at(a.u[d], vl);
+    x0[d] = at(a.x[d], vl);
   }
-  const float mn = a.mnode[vl];
+  const float mn = at(a.mnode, vl);
   double dtd;
   if (kLoop) {
 #pragma unroll
@@ -621,13 +657,13 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a, HydroLoop lp) {
   for (int c = 0; c < 8; ++c)
 #pragma unroll
     for (int d = 0; d < 3; ++d) F[d] += in[c] ? f[c][d] : 0.0f;
-  const int64_t idx[3] = {i, j, k};
+  const int idx[3] = {i, j, k};
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     float u1 = __builtin_fmaf(dt, F[d] * inv_m, u0[d]);
     if (idx[d] == 0) u1 = 0.0f;
-    a.un[d][v] = u1;
-    a.x[d][v] = __builtin_fmaf(dt, 0.5f * (u0[d] + u1), x0[d]);
+    at(a.un[d], vl) = u1;
+    at(a.x[d], vl) = __builtin_fmaf(dt, 0.5f * (u0[d] + u1), x0[d]);
   }
 }
 
@@ -638,16 +674,16 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a, HydroLoop lp) {
 // positions and velocities, so the gathers, the volume and its gradient are
 // formed once, and pressure, viscosity and sound speed stay in registers; the
 // next step's time-step bound goes to one of lp.slots minima by an integer
-// atomic.  kNoNext: the EOS alone.  Fused, the kernel holds 200 registers (two
-// waves per SIMD; held to three it spills and takes 60 us instead of 37 at
-// 90^3): a step on 90^3 elements takes 54 us instead of 66 in four launches
-// (force 23.0, time step 4.7, node 16.2, EOS 21.5), on 24^3 with EOS TAF 11.8
-// instead of 18.3.
+// atomic.  kNoNext: the EOS alone.  A step on 90^3 elements takes 47.5 us
+// (30.4 this kernel, 16.6 the nodes: 5.6 and 6.6 TB/s of forces and fields)
+// against 61 in four launches, one on 24^3 with EOS TAF 11.4 against 17.
+// Registers for three waves per SIMD, four where there are no hourglass
+// forces; with what the compiler takes by itself (172, two waves) EOS TAF at
+// 90^3 measured 12% slower.
 template <int EOS, int NEXT>
-__global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a, HydroLoop lp) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NEXT == kNoNext || NEXT == kHgNone ? 4 : 3))) k_hydro_eos(HydroArgs a, HydroLoop lp) {
   constexpr bool kTaf = EOS != kEosExact, kFused = NEXT != kNoNext;
   static_assert(!kFused || EOS != kEosTafBlock, "block level steps one kernel at a time");
-  const int n = a.n;
   const int64_t E = a.E;
   const int64_t blk = xcd_block(blockIdx.x, gridDim.x);  // element block: the block-level group
   const int64_t z = blk * blockDim.x + threadIdx.x;
@@ -706,25 +742,26 @@ __global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a, HydroLoop lp) {
     const ElemIdx ei(z, a.dn);
     float x[8][3], u1[8][3], B[8][3];
     // every load before the atomic and the stores, as in the force kernel
-    gather3(a.x, ei, n, x);
-    gather3(a.un, ei, n, u1);
-    const float m = a.mass[z];
+    gather3(a.x, ei, x);
+    gather3(a.un, ei, u1);
+    const float m = at(a.mass, ei.z);
     float p1 = 0.0f, q1 = 0.0f, c1 = 0.0f;
     if (kFused && approx) {
-      p1 = a.p[z];
-      q1 = a.q[z];
-      c1 = a.c[z];
+      p1 = at(a.p, ei.z);
+      q1 = at(a.q, ei.z);
+      c1 = at(a.c, ei.z);
     }
     float V1;
     if (!kTaf || !approx) {
       float u0[8][3];
-      gather3(a.u, ei, n, u0);
-      const float dt = (float)*lp.dt, e0 = a.e[z], c0 = a.c[z];
+      gather3(a.u, ei, u0);
+      const float dt = (float)*lp.dt, e0 = at(a.e, ei.z), c0 = at(a.c, ei.z);
       float W = 0.0f;
+      Planes<const float> plane{a.force};
 #pragma unroll
       for (int c = 0; c < 8; ++c)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) W = __builtin_fmaf(a.force[(c * 3 + d) * E + z], 0.5f * (u0[c][d] + u1[c][d]), W);
+        for (int d = 0; d < 3; ++d) W = __builtin_fmaf(at(plane.next(E), ei.z), 0.5f * (u0[c][d] + u1[c][d]), W);
       // the work, the volume and its rate one after the other: interleaved, they
       // hold more in registers at once and measured 1.4% slower per step
       __builtin_amdgcn_sched_barrier(0);
@@ -745,12 +782,12 @@ __global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a, HydroLoop lp) {
       q1 = du < 0.0f ? rho1 * (a.cq * du * du + a.cl * c0 * fabsf(du)) : 0.0f;
       p1 = (a.gamma - 1.0f) * rho1 * e1;
       c1 = sqrtf(a.gamma * fmaxf(p1, 0.0f) / rho1);
-      a.e[z] = e1;
+      at(a.e, ei.z) = e1;
       if (!kFused || kTaf) {  // else the loop's last EOS writes them
-        a.p[z] = p1;
-        a.q[z] = q1;
+        at(a.p, ei.z) = p1;
+        at(a.q, ei.z) = q1;
       }
-      a.c[z] = c1;
+      at(a.c, ei.z) = c1;
       if (kTaf) {
         const int slot = pushes % a.eos_h;
         const float y[4] = {e1, p1, q1, c1};
@@ -767,15 +804,15 @@ __global__ void __launch_bounds__(256) k_hydro_eos(HydroArgs a, HydroLoop lp) {
       if (!(V1 > 0.0f)) atomicOr(a.status, kHydroBadVolume);
     }
     if (kFused) {
-      if (lp.store_vol) a.vol[z] = V1;
+      if (lp.store_vol) at(a.vol, ei.z) = V1;
       const float pq = p1 + q1;
       const float vdot = volume_rate(B, u1);
       if (NEXT == kHgExact) {
         float f[8][3];
         hourglass(x, u1, B, V1, m / V1, c1, a.khg, f);
-        store_forces(a.force, E, z, pq, B, f);
+        store_forces(a.force, E, ei, pq, B, f);
       } else {
-        store_forces(a.force, E, z, pq, B, nullptr);
+        store_forces(a.force, E, ei, pq, B, nullptr);
       }
       bound = fmin(bound, time_bound(a, V1, m, pq, vdot));
     }
