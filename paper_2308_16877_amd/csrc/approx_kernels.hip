@@ -244,27 +244,53 @@ struct IsPaired : std::false_type {};
 template <class R>
 struct IsPaired<R, std::void_t<decltype(R::kPaired)>> : std::bool_constant<R::kPaired> {};
 
-// Exact path of a paired region, uncounted, items per lane >= 2: steps k and
-// k + 1 of a lane go through one packed evaluation.  Same lanes and items as
-// k_exact; an odd last step is paired with a copy of itself.
-template <class R>
-__global__ void __launch_bounds__(256) k_exact_pairs(KArgs a) {
-  const LaneGeom g;
-  for (int k = 0; k < a.ipt; k += 2) {
-    if (!g.wave_has(a, k)) return;
-    const bool act0 = g.active(a, k);
-    const bool act1 = k + 1 < a.ipt && g.active(a, k + 1);
-    float x0[R::kIn], x1[R::kIn];
-    if (act0) load_inputs<R>(a, g.item(a, k), x0);
-    if (act1) load_inputs<R>(a, g.item(a, k + 1), x1);
-    if (act0) {
-      if (!act1)
+// Exact path, uncounted, on 16-bit columns: V adjacent items per lane, a
+// column's V elements one load, a pair of items through one packed evaluation
+// where the region has one.  The region keeps no state, so which lane
+// evaluates an item does not matter.  Bound by HBM: 2^24 items of the FP16
+// body 47.3 us (4.97 TB/s), where two items 2^23 apart per lane took 58.8
+// and one item per lane 52.9; four or eight adjacent items measured 44.7 to
+// 49 by body, no better over the sizes.
+template <class R, int V>
+__global__ void __launch_bounds__(256) k_exact_run(KArgs a) {
+  using elem = typename R::io::elem;
+  typedef elem vec __attribute__((ext_vector_type(V)));
+  const int64_t first = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * V;
+  if (first + V <= a.n) {
+    float x[V][R::kIn], y[V][R::kOut];
 #pragma unroll
-        for (int j = 0; j < R::kIn; ++j) x1[j] = x0[j];
-      float y0[R::kOut], y1[R::kOut];
-      R::eval2(x0, x1, y0, y1);
-      store_outputs<R>(a, g.item(a, k), y0);
-      if (act1) store_outputs<R>(a, g.item(a, k + 1), y1);
+    for (int j = 0; j < R::kIn; ++j) {
+      const vec e = *(const vec *)((const elem *)a.in[j] + first);
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const elem t = e[q];
+        x[q][j] = R::io::load(&t, 0);
+      }
+    }
+    if constexpr (IsPaired<R>::value) {
+#pragma unroll
+      for (int q = 0; q < V; q += 2) R::eval2(x[q], x[q + 1], y[q], y[q + 1]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < V; ++q) R::eval(x[q], y[q]);
+    }
+#pragma unroll
+    for (int o = 0; o < R::kOut; ++o) {
+      vec e;
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        elem t;
+        R::io::store(&t, 0, y[q][o]);
+        e[q] = t;
+      }
+      *(vec *)((elem *)a.out[o] + first) = e;
+    }
+  } else {
+    for (int64_t i = first; i < a.n; ++i) {
+      float x[R::kIn], y[R::kOut];
+      load_inputs<R>(a, i, x);
+      R::eval(x, y);
+      store_outputs<R>(a, i, y);
     }
   }
 }
@@ -830,26 +856,66 @@ static hipError_t with_region(int region, int dtype, const F &f) {
   }
 }
 
+// A dispatch's grid size is a 32-bit count of lanes per dimension; the
+// second and third dimensions are kept within 65535 workgroups.
+constexpr int64_t kMaxGridLanes = 0xFFFFFFFFll;
+constexpr int64_t kMaxGridYZ = 65535;
+
+// Items per lane of k_exact_run and the batch from which it is taken: below,
+// half as many waves leave the chip less to overlap (FP16 body, 4.2M items:
+// 13.4 us against 12.6 with one item per lane; 6M: 20.0 against 22.3).
+constexpr int kRunItems = 2;
+constexpr int64_t kRunFrom = 5 << 20;
+// FP32 batches of this range keep the caller's items per lane: there the
+// strided sweep with streaming accesses, with fewer workgroups to start, is
+// the faster one at four and more (4.2M items: 22.0 us at 16 per lane against
+// 23.6 at one; 2M: 14.2 against 10.3; 8.4M: 43.2 against 40.6).  The FP32
+// body on FP16 columns keeps them from kStridedMixed on (2^24 items: 53.3 us
+// against 55.5; 10M: 37.4 against 35.1).
+constexpr int64_t kStridedFrom = 5 << 19, kStridedTo = 7 << 20, kStridedMixed = 3 << 22;
+
 struct ExactL {
   const LaunchCfg &c;
   const KArgs &a;
   template <class R>
   hipError_t go() const {
-    if (a.ipt > 1) return run<Streamed<R>>();
-    return run<R>();
+    if (a.trace || a.counters) {
+      // items per lane are part of what these report
+      if (a.ipt > 1) return counted<Streamed<R>>();
+      return counted<R>();
+    }
+    // The exact region keeps no state, so its outputs do not depend on the
+    // mapping of items to lanes: one contiguous sweep whatever the items per
+    // lane (2^24 FP32 items: 77 us; 83 at 16 items per lane, whose items
+    // lie 2^20 apart; 30,000 items 3.1 against 6.7).
+    constexpr int esz = sizeof(typename R::io::elem);
+    // the FP32 body on FP16 columns keeps its one-item kernel: the mixed-precision
+    // instructions it compiles to round some results differently in pairs
+    constexpr bool mixed = std::is_base_of<RegionBSPrice, R>::value && std::is_same<typename R::io, IoF16>::value;
+    if constexpr (esz == 2 && !mixed) {
+      bool aligned = true;
+      for (int j = 0; j < R::kIn; ++j) aligned &= (uintptr_t)a.in[j] % (esz * kRunItems) == 0;
+      for (int o = 0; o < R::kOut; ++o) aligned &= (uintptr_t)a.out[o] % (esz * kRunItems) == 0;
+      const int64_t blocks = (a.n + (int64_t)kRunItems * c.block - 1) / ((int64_t)kRunItems * c.block);
+      if (aligned && a.n >= kRunFrom && blocks * c.block <= kMaxGridLanes) {
+        hipLaunchKernelGGL((k_exact_run<R, kRunItems>), dim3((unsigned)blocks), dim3(c.block), 0, c.stream, a);
+        return hipGetLastError();
+      }
+    }
+    KArgs b = a;
+    b.ipt = 1;
+    b.L = (a.n + 63) / 64 * 64;
+    const bool strided =
+        a.ipt >= 4 && (mixed ? a.n >= kStridedMixed : esz == 4 && a.n >= kStridedFrom && a.n < kStridedTo);
+    if (!strided && (b.L + c.block - 1) / c.block * c.block <= kMaxGridLanes)
+      hipLaunchKernelGGL((k_exact<R, false>), grid_for(b, c.block), dim3(c.block), 0, c.stream, b);
+    else
+      hipLaunchKernelGGL((k_exact<Streamed<R>, false>), grid_for(a, c.block), dim3(c.block), 0, c.stream, a);
+    return hipGetLastError();
   }
   template <class R>
-  hipError_t run() const {
-    if (a.trace || a.counters)
-      hipLaunchKernelGGL((k_exact<R, true>), counted_grid(a, c.block), dim3(c.block), 0, c.stream, a);
-    else if constexpr (IsPaired<R>::value) {
-      if (a.ipt >= 2)
-        hipLaunchKernelGGL((k_exact_pairs<R>), grid_for(a, c.block), dim3(c.block), 0, c.stream, a);
-      else
-        hipLaunchKernelGGL((k_exact<R, false>), grid_for(a, c.block), dim3(c.block), 0, c.stream, a);
-    } else {
-      hipLaunchKernelGGL((k_exact<R, false>), grid_for(a, c.block), dim3(c.block), 0, c.stream, a);
-    }
+  hipError_t counted() const {
+    hipLaunchKernelGGL((k_exact<R, true>), counted_grid(a, c.block), dim3(c.block), 0, c.stream, a);
     return hipGetLastError();
   }
 };
@@ -857,11 +923,6 @@ struct ExactL {
 hipError_t launch_exact(const LaunchCfg &c, const KArgs &a) {
   return with_region<true>(c.region, c.dtype, ExactL{c, a});
 }
-
-// A dispatch's grid size is a 32-bit count of lanes per dimension; the
-// second and third dimensions are kept within 65535 workgroups.
-constexpr int64_t kMaxGridLanes = 0xFFFFFFFFll;
-constexpr int64_t kMaxGridYZ = 65535;
 
 struct PerfoL {
   const LaunchCfg &c;

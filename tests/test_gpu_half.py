@@ -170,3 +170,50 @@ def test_packed_fp16_pairs_equal_single_items(dtype):
         ys[ipt] = np.stack([o.float().cpu().numpy() for o in out])
     for ipt in (2, 3, 16):
         assert np.array_equal(ys[ipt], ys[1]), ipt
+
+
+@pytest.mark.parametrize("region,dtype", [(hpac.REGION_BS_PRICE_F16, hpac.F16), (hpac.REGION_BS_PRICE, hpac.F16),
+                                          (hpac.REGION_BS_PRICE, hpac.BF16), (hpac.REGION_BS_PRICE_BF16, hpac.BF16)])
+@pytest.mark.parametrize("extra", [0, 1, 513])
+def test_adjacent_pairs_equal_single_items(region, dtype, extra):
+    """From 5 * 2^20 items on, two adjacent items go through one load per
+    column (and one packed evaluation of the FP16 body): every output equals
+    that of the same items in batches of one item per lane, with odd counts
+    (the last lane has one item) and with columns that start at an odd
+    element, which takes the one-item path."""
+    n = 5 * (1 << 20) + extra
+    g = torch.Generator(device=DEV).manual_seed(7)
+    lo, hi = (torch.tensor(v, device=DEV, dtype=torch.float32) for v in (inputs.BOX_LO, inputs.BOX_HI))
+    x = [(lo[j] + (hi[j] - lo[j]) * torch.rand(n, generator=g, device=DEV)).to(TYPES[dtype]) for j in range(5)]
+
+    def outs(m):
+        return [torch.full((m,), -7.0, dtype=TYPES[dtype], device=DEV) for _ in range(2)]
+
+    y, z, w = outs(n), outs(n), outs(n + 1)
+    hpac.hpac_exact(x, y, region=region, items_per_lane=2)
+    for a in range(0, n, 1 << 22):
+        b = min(a + (1 << 22), n)
+        hpac.hpac_exact([c[a:b] for c in x], [c[a:b] for c in z], region=region)
+    odd = [torch.cat([c[:1], c])[1:] for c in x]
+    assert all(c.data_ptr() % 4 == 2 for c in odd)
+    hpac.hpac_exact(odd, [c[1:] for c in w], region=region)
+    torch.cuda.synchronize()
+    for o in range(2):
+        assert torch.equal(y[o], z[o]) and torch.equal(y[o], w[o][1:]) and float(w[o][0]) == -7.0
+
+
+@pytest.mark.parametrize("n", [1, 63, 4097, 5 * (1 << 19) - 1, 5 * (1 << 19), 7 * (1 << 20)])
+def test_exact_outputs_do_not_depend_on_items_per_lane(n):
+    """One, four and sixteen items per lane give the same outputs, on either
+    side of the batch sizes where the launch keeps the caller's mapping."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    lo, hi = (torch.tensor(v, device=DEV, dtype=torch.float32) for v in (inputs.BOX_LO, inputs.BOX_HI))
+    x = [lo[j] + (hi[j] - lo[j]) * torch.rand(n, generator=g, device=DEV) for j in range(5)]
+    ys = []
+    for ipt in (1, 4, 16):
+        y = [torch.full((n,), -7.0, device=DEV) for _ in range(2)]
+        hpac.hpac_exact(x, y, items_per_lane=ipt)
+        ys.append(y)
+    torch.cuda.synchronize()
+    for y in ys[1:]:
+        assert torch.equal(y[0], ys[0][0]) and torch.equal(y[1], ys[0][1])
