@@ -529,13 +529,16 @@ static hipError_t infer_go(const MlpArgs &a, int64_t resident, hipStream_t strea
 }
 
 hipError_t launch_mlp_infer(const MlpArgs &a, hipStream_t stream) {
-  // one resident wave per SIMD slot the kernel's register use allows
-  int dev = 0, cus = 0, per_cu = 0;
+  // one resident wave per SIMD slot the kernel's register use allows; a batch
+  // of at most one workgroup per CU is resident whatever that is
+  int dev = 0, cus = 0, per_cu = 1;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_infer<4>, 256, 0);
+  if (cus < 1) cus = 1;
+  if (e == hipSuccess && a.n > (int64_t)cus * 256)
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_mlp_infer<4>, 256, 0);
   if (e != hipSuccess) return e;
-  const int64_t resident = (int64_t)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
+  const int64_t resident = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
   hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(1), 0, stream, a.queue_count);
   // one tile per wave while that is at most one workgroup per CU: four tiles in
   // a row are then latency no other wave hides (12,000 items: 8.8 us against

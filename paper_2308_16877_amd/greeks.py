@@ -48,6 +48,9 @@ class GreeksFn(torch.autograd.Function):
             ctx.save_for_backward(*outs[2:])
             ctx.mode = "vjp"
         ctx.n = n
+        # an output without an upstream gradient reaches the backward as None,
+        # which the kernels read as zero: no column of zeros filled and read back
+        ctx.set_materialize_grads(False)
         return C, P
 
     @staticmethod
@@ -55,6 +58,8 @@ class GreeksFn(torch.autograd.Function):
         saved = ctx.saved_tensors
         dev = saved[0].device
         grads = [torch.empty(ctx.n, dtype=torch.float32, device=dev) for _ in range(5)]
+        if gC is None and gP is None:
+            gC = torch.zeros(ctx.n, dtype=torch.float32, device=dev)
         gC = gC.contiguous().to(torch.float32) if gC is not None else None
         gP = gP.contiguous().to(torch.float32) if gP is not None else None
         if ctx.mode == "adjoint":

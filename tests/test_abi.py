@@ -353,3 +353,38 @@ def test_source_item_region_arguments():
     with pytest.raises(ValueError, match="source"):
         hpac.hpac_exact([FAKE] * 5, [FAKE, FAKE, torch.zeros(999, dtype=torch.int32)], n=1000,
                         region=hpac.REGION_BS_PRICE_REF)
+
+
+def _outcome(f, *args):
+    try:
+        return f(*args)
+    except Exception as e:
+        return type(e), str(e)
+
+
+def test_column_and_buffer_checks_agree_with_the_general_checks(monkeypatch):
+    import numpy as np
+    import torch
+
+    class Sub(torch.Tensor):
+        pass
+
+    n = 6
+    base = torch.arange(24, dtype=torch.float32)
+    forms = [base[:n], base[:12:2], base[:n + 1], base[:0], base.reshape(4, n)[1], base.reshape(4, n).t()[0],
+             base[:n].reshape(2, 3), base[:n].reshape(1, n), base[0], base[:n].as_subclass(Sub),
+             torch.nn.Parameter(base[:n]), base[:1].expand(n), 4096, True, None, "column", np.arange(n, dtype=np.float32)]
+    forms += [base[:n].to(t) for t in (torch.float16, torch.bfloat16, torch.float64, torch.int8, torch.uint8, torch.int32,
+                                       torch.int64, torch.uint32, torch.uint64, torch.bool)]
+    hpac._load_torch()
+    for t in forms:
+        for dtype in (hpac.F32, hpac.F16, hpac.BF16, None, 7):
+            assert _outcome(hpac._check_columns, [4096, t], n, dtype) == _outcome(hpac._check_column, t, n, dtype), t
+        for kind in hpac._KINDS:
+            for need in (0, n, n + 1, 4 * n):
+                quick = _outcome(hpac._check_buf, t, need, kind, "buf")
+                with monkeypatch.context() as m:
+                    m.setattr(hpac, "_torch", None)
+                    assert quick == _outcome(hpac._check_buf, t, need, kind, "buf"), (t, kind, need)
+        if not isinstance(t, (str, np.ndarray)):
+            assert _outcome(hpac._addrs, [t]) == _outcome(lambda: [hpac._addr(t)])

@@ -263,3 +263,32 @@ def test_autograd_greeks_against_closed_forms(technique):
         for j in range(5):
             assert np.all(np.abs(gcall[j].cpu().numpy() - ora["out"][2 + j]) <= 1e-5 * ora["scale"][2 + j] + 1e-30)
             assert np.all(np.abs(gput[j].cpu().numpy() - ora["out"][7 + j]) <= 1e-5 * ora["scale"][7 + j] + 1e-30)
+
+
+@pytest.mark.parametrize("technique", ["exact", "iact", "iact_jacobian"])
+def test_missing_upstream_equals_zeros(technique):
+    # an output nothing depends on has no upstream gradient: the same bits as
+    # an upstream of zeros, and zeros where neither output has one
+    params = None if technique == "exact" else dict(table_size=4, threshold=0.05)
+    x = [c.requires_grad_() for c in to_dev(inputs.uniform_box(1031, 11))]
+    g = torch.linspace(-1, 1, 1031, device=DEV)
+    zero = torch.zeros_like(g)
+    for up in ((g, None), (None, g)):
+        out = bs_prices(*x, technique=technique, params=params)
+        used = [(o, u) for o, u in zip(out, up) if u is not None]
+        got = torch.autograd.grad([o for o, _ in used], x, [u for _, u in used])
+        out = bs_prices(*x, technique=technique, params=params)
+        want = torch.autograd.grad(out, x, [zero if u is None else u for u in up])
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+    class Sever(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, a, b):
+            return a + b
+
+        @staticmethod
+        def backward(ctx, upstream):
+            return None, None
+
+    got = torch.autograd.grad(Sever.apply(*bs_prices(*x, technique=technique, params=params)), x, g)
+    assert all(torch.equal(a, zero) for a in got)
