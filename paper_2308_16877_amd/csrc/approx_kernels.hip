@@ -749,8 +749,9 @@ __global__ void __launch_bounds__(256) k_taf_wave(KArgs a, int psize, float thet
     const uint64_t vmask = ballot(crit);
     const bool any_vote = ballot(voted) != 0;
     const bool pass = any_vote && majority(popc(vmask), popc(amask));
-    const int next = pass ? k + psize + 1 : k + 1;
-    if ((prev_pass || pass) && next < a.ipt && g.active(a, next)) load_inputs<R>(a, g.item(a, next), xn);
+    // 64 bits: the prediction size may be any positive int
+    const int64_t next = (int64_t)k + (pass ? psize : 0) + 1;
+    if ((prev_pass || pass) && next < a.ipt && g.active(a, (int)next)) load_inputs<R>(a, g.item(a, (int)next), xn);
     if (a.trace || a.counters) {
       st.add(popc(amask), 0, false);
       if (a.trace && lane == 0)
@@ -768,10 +769,10 @@ __global__ void __launch_bounds__(256) k_taf_wave(KArgs a, int psize, float thet
           if (a.trace && lane == 0) a.trace[g.trace_index(a, kk)] = trace_word(0, nact, -1, true, false);
         }
       }
-      left = next - kk;
+      left = (int)(next - kk);
     }
     prev_pass = pass;
-    k = next;
+    k = next < a.ipt ? (int)next : a.ipt;
   }
   if (kState && g.l < a.L) ts.store(g.l, win, fill, left);
   sink.end(st);

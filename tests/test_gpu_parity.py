@@ -596,3 +596,18 @@ def test_full_size_config_against_oracle():
     # the dense kernel the benchmark times: the same outputs, dropped items untouched
     yu, _, _ = run("perfo", xd, 2, 20, trace=False, counters=False, kind="small", param=10)
     assert np.array_equal(yu, yp)
+
+
+def test_taf_longest_prediction_covers_the_rest():
+    # a prediction size of the type's maximum: every step after the vote is
+    # approximate, as with one of the remaining steps
+    n, ipt = 64 * 9 * 3, 9
+    x = [torch.full((n,), float(v), device=DEV) for v in (20.0, 25.0, 1.0, 0.02, 0.3)]
+    got = []
+    for p in (2 ** 31 - 1, ipt):
+        out = [torch.full((n,), SENTINEL, device=DEV) for _ in range(2)]
+        trace = torch.zeros(hpac.hpac_trace_entries(n, ipt), dtype=torch.int32, device=DEV)
+        hpac.hpac_taf(x, out, history_size=2, prediction_size=p, rsd_threshold=0.01, items_per_lane=ipt, trace=trace)
+        got.append(out + [trace])
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    assert not any((o == SENTINEL).any() for o in got[0][:2])
