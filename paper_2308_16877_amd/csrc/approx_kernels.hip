@@ -693,6 +693,8 @@ __global__ void __launch_bounds__(256) k_taf_wave(KArgs a, int psize, float thet
   sink.begin();
   const double th = (double)theta;
   const double th2 = th * th;
+  using Next = std::conditional_t<kState, int64_t, uint32_t>;
+  if (!kState && psize > a.ipt) psize = a.ipt;  // more steps than there are
   float win[H][R::kOut];  // win[H-1] is the newest accurate output
 #pragma unroll
   for (int q = 0; q < H; ++q)
@@ -749,9 +751,10 @@ __global__ void __launch_bounds__(256) k_taf_wave(KArgs a, int psize, float thet
     const uint64_t vmask = ballot(crit);
     const bool any_vote = ballot(voted) != 0;
     const bool pass = any_vote && majority(popc(vmask), popc(amask));
-    // 64 bits: the prediction size may be any positive int
-    const int64_t next = (int64_t)k + (pass ? psize : 0) + 1;
-    if ((prev_pass || pass) && next < a.ipt && g.active(a, (int)next)) load_inputs<R>(a, g.item(a, (int)next), xn);
+    // with a state 64 bits: the prediction size may be any positive int, and
+    // what is left of it is carried on
+    const Next next = (Next)k + (pass ? psize : 0) + 1;
+    if ((prev_pass || pass) && next < (Next)a.ipt && g.active(a, (int)next)) load_inputs<R>(a, g.item(a, (int)next), xn);
     if (a.trace || a.counters) {
       st.add(popc(amask), 0, false);
       if (a.trace && lane == 0)
@@ -760,7 +763,7 @@ __global__ void __launch_bounds__(256) k_taf_wave(KArgs a, int psize, float thet
     left = 0;
     if (pass) {
       int kk = k + 1;
-      for (; kk < next && kk < a.ipt && g.wave_has(a, kk); ++kk) {
+      for (; (Next)kk < next && kk < a.ipt && g.wave_has(a, kk); ++kk) {
         const bool act = g.active(a, kk);
         if (act) store_outputs<R>(a, g.item(a, kk), win[H - 1]);
         if (a.trace || a.counters) {
@@ -772,10 +775,96 @@ __global__ void __launch_bounds__(256) k_taf_wave(KArgs a, int psize, float thet
       left = (int)(next - kk);
     }
     prev_pass = pass;
-    k = next < a.ipt ? (int)next : a.ipt;
+    k = next < (Next)a.ipt ? (int)next : a.ipt;
   }
   if (kState && g.l < a.L) ts.store(g.l, win, fill, left);
   sink.end(st);
+}
+
+// Wave-level TAF for small grids, uncounted and without a state: one workgroup
+// of kTeam waves per logical wave, wave w of it evaluating step w of each run of
+// kTeam steps.  All of a run's steps are evaluated and their criteria formed as
+// if every step were accurate; the first vote that passes fixes the steps up to
+// it and the approximate ones behind it, and the criteria of the steps behind
+// those are formed anew, until no vote passes.  The same values, windows and
+// decisions as k_taf_wave.  That kernel is bound at small grids by the
+// instructions a lone wave issues one after another, 0.63 us a step, while most
+// SIMDs are idle: 65,536 items at 16 per lane 11.7 us there, 4.0 here.
+constexpr int kTeam = 16;
+// outputs of the accurate steps, a ring by their sequence number: a run's, and
+// the window before it
+constexpr int kTeamRows = 32;
+
+template <class R, int H>
+__global__ void __launch_bounds__(64 * kTeam) k_taf_team(KArgs a, int psize, float theta) {
+  static_assert(kTeamRows >= kTeam + H, "a run's outputs and the window before it");
+  __shared__ float ring[kTeamRows][R::kOut][kWave];
+  __shared__ uint32_t passed[3];  // votes that pass, of this round, the last and the next
+  const int lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t wbase = (int64_t)blockIdx.x * kWave, l = wbase + lane;
+  const double th = (double)theta;
+  const double th2 = th * th;
+  if (psize > a.ipt) psize = a.ipt;  // more steps than there are
+  // where a vote can make the whole next run approximate, its inputs wait for it
+  const bool late = psize >= kTeam;
+  if (threadIdx.x < 3) passed[threadIdx.x] = 0;
+  auto load = [&](int k, float (&x)[R::kIn]) {
+    const int64_t i = l + (int64_t)k * a.L;
+    load_inputs<R>(a, i < a.n ? i : a.n - 1, x);
+  };
+  float x[R::kIn];
+  load(w, x);
+  int base = 0;   // accurate steps so far
+  int start = 0;  // the run's first step that is not approximate by an earlier vote
+  int slot = 0;
+  for (int run = 0; run < a.ipt && wbase + (int64_t)run * a.L < a.n; run += kTeam) {
+    const int k = run + w;
+    const int64_t i = l + (int64_t)k * a.L;
+    const bool has = k < a.ipt && i - lane < a.n, active = has && i < a.n;
+    float y[R::kOut];
+    if (w < start) {
+#pragma unroll
+      for (int o = 0; o < R::kOut; ++o) y[o] = ring[(base - 1) % kTeamRows][o][lane];
+      if (active) store_outputs<R>(a, i, y);
+    } else {
+      R::eval(x, y);
+    }
+    if (!late) load(k + kTeam, x);
+    while (start < kTeam) {
+      // every wave takes part in the barriers; those decided already do no more
+      const int p = base + w - start;  // this step's number among the accurate ones
+      if (w >= start)
+#pragma unroll
+        for (int o = 0; o < R::kOut; ++o) ring[p % kTeamRows][o][lane] = y[o];
+      if (threadIdx.x == 0) passed[(slot + 1) % 3] = 0;
+      __syncthreads();
+      if (w >= start && p + 1 >= H) {
+        float win[H][R::kOut];
+#pragma unroll
+        for (int q = 0; q < H; ++q)
+#pragma unroll
+          for (int o = 0; o < R::kOut; ++o) win[q][o] = ring[(p - (H - 1) + q) % kTeamRows][o][lane];
+        const bool crit = active && rsd_below<H, R::kOut>(win, th2, th > 0.0);
+        if (majority(popc(ballot(crit)), popc(ballot(active))) && lane == 0) atomicOr(&passed[slot], 1u << w);
+      }
+      __syncthreads();
+      const uint32_t votes = __builtin_amdgcn_readfirstlane(passed[slot]);
+      slot = slot == 2 ? 0 : slot + 1;
+      const int first = votes ? __builtin_ctz(votes) : kTeam;
+      const int next = votes ? first + psize + 1 : kTeam;
+      if (w >= start && w < next) {
+        if (w > first)
+#pragma unroll
+          for (int o = 0; o < R::kOut; ++o) y[o] = ring[(base + first - start) % kTeamRows][o][lane];
+        if (active) store_outputs<R>(a, i, y);
+      }
+      base += (votes ? first + 1 : kTeam) - start;
+      start = next;
+    }
+    start -= kTeam;
+    if (late && w >= start) load(k + kTeam, x);
+  }
 }
 
 // ------------------------------------------------------------------ probe
@@ -875,6 +964,21 @@ constexpr int64_t kRunFrom = 5 << 20;
 // against 55.5; 10M: 37.4 against 35.1).
 constexpr int64_t kStridedFrom = 5 << 19, kStridedTo = 7 << 20, kStridedMixed = 3 << 22;
 
+// The FP32 body on FP16 columns: the mixed-precision instructions it compiles
+// to round some results differently in each kernel, so it keeps to one kernel
+// per path.
+template <class R>
+constexpr bool kMixed =
+    std::is_base_of<RegionBSPrice, R>::value && std::is_same<typename R::io::elem, _Float16>::value;
+
+// Fewest items per lane and most lanes of k_taf_team.  With more lanes the
+// SIMDs are filled without it, and the steps evaluated for nothing show (votes
+// that fail / pass, at 16 items per lane and 2^14 lanes: 4.5 / 5.6 us against
+// 12.4 / 7.0; at 64 and 2^15: 13.3 / 21.9 against 45.1 / 18.2); with fewer steps
+// there is no chain to shorten (3 per lane: 4.3 us both).
+constexpr int kTeamFrom = 4;
+constexpr int64_t kTeamLanes = 1 << 14;
+
 struct ExactL {
   const LaunchCfg &c;
   const KArgs &a;
@@ -890,9 +994,7 @@ struct ExactL {
     // lane (2^24 FP32 items: 77 us; 83 at 16 items per lane, whose items
     // lie 2^20 apart; 30,000 items 3.1 against 6.7).
     constexpr int esz = sizeof(typename R::io::elem);
-    // the FP32 body on FP16 columns keeps its one-item kernel: the mixed-precision
-    // instructions it compiles to round some results differently in pairs
-    constexpr bool mixed = std::is_base_of<RegionBSPrice, R>::value && std::is_same<typename R::io, IoF16>::value;
+    constexpr bool mixed = kMixed<R>;
     if constexpr (esz == 2 && !mixed) {
       bool aligned = true;
       for (int j = 0; j < R::kIn; ++j) aligned &= (uintptr_t)a.in[j] % (esz * kRunItems) == 0;
@@ -1018,6 +1120,12 @@ hipError_t launch_iact(const LaunchCfg &c, const KArgs &a, int level, int table_
 template <class R, int LEVEL, int H>
 static void taf_go(const LaunchCfg &c, const KArgs &a, int p, float thr, float *st) {
   if constexpr (LEVEL == kWaveLvl) {
+    if constexpr (!kMixed<R> && R::kOut <= 2)
+      if (!st && !a.trace && !a.counters && a.ipt >= kTeamFrom && a.L <= kTeamLanes) {
+        hipLaunchKernelGGL((k_taf_team<R, H>), dim3((unsigned)(a.L / kWave)), dim3(kWave * kTeam), 0, c.stream, a, p,
+                           thr);
+        return;
+      }
     if (st)
       hipLaunchKernelGGL((k_taf_wave<R, H, true>), grid_for(a, c.block), dim3(c.block), 0, c.stream, a, p, thr, st);
     else

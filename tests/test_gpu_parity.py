@@ -611,3 +611,32 @@ def test_taf_longest_prediction_covers_the_rest():
         got.append(out + [trace])
     assert all(torch.equal(a, b) for a, b in zip(*got))
     assert not any((o == SENTINEL).any() for o in got[0][:2])
+
+
+@pytest.mark.parametrize("dtype,region", [("f32", hpac.REGION_BS_PRICE), ("f16", hpac.REGION_BS_PRICE_F16),
+                                          ("bf16", hpac.REGION_BS_PRICE), ("bf16", hpac.REGION_BS_PRICE_BF16),
+                                          ("f32", hpac.REGION_BS_PRICE_F16)])
+@pytest.mark.parametrize("h,p,theta", [(1, 1, 0.01), (2, 4, 0.0), (4, 4, 0.01), (3, 15, 0.02), (5, 16, 0.02), (8, 40, 0.05),
+                                       (4, 2 ** 31 - 1, 0.02)])
+def test_taf_teams_equal_single_waves(dtype, region, h, p, theta):
+    # a traced launch keeps one wave per 64 lanes; without a trace, small grids
+    # take a workgroup for them: the same outputs, bit for bit, whatever runs the
+    # votes form and wherever a run of sixteen steps is cut
+    dt = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    gen = torch.Generator().manual_seed(100 * h + p % 97)
+    lo, hi = torch.tensor(inputs.BOX_LO), torch.tensor(inputs.BOX_HI)
+    for n, ipt in ((1, 4), (63, 5), (64 * 16, 16), (64 * 17 - 5, 17), (5000, 33), (20011, 64), (64 * 40 + 1, 40)):
+        lanes = hpac.hpac_num_lanes(n, ipt)
+        k = torch.arange(n) // lanes
+        # the contract of a wave's lanes changes every few steps, jittered so that some windows pass
+        group = (k + 3 * ((torch.arange(n) % lanes) // 64)) // torch.randint(1, 25, (1,), generator=gen)
+        pool = lo[:, None] + (hi - lo)[:, None] * torch.rand(5, int(group.max()) + 1, generator=gen, dtype=torch.float64)
+        x = pool[:, group] * (1 + 0.01 * torch.randn(5, n, generator=gen, dtype=torch.float64))
+        cols = [c.to(dt).to(DEV) for c in x]
+        got, want = ([torch.full((n,), -7.0, dtype=dt, device=DEV) for _ in range(2)] for _ in range(2))
+        trace = torch.zeros(hpac.hpac_trace_entries(n, ipt), dtype=torch.int32, device=DEV)
+        kw = dict(history_size=h, prediction_size=p, rsd_threshold=theta, items_per_lane=ipt, region=region)
+        hpac.hpac_taf(cols, want, trace=trace, **kw)
+        hpac.hpac_taf(cols, got, **kw)
+        for a, b in zip(got, want):
+            assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), (n, ipt)
