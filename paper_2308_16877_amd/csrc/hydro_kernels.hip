@@ -852,7 +852,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NEXT =
     __shared__ double mins[4];
 #pragma unroll
     for (int s = 1; s < 64; s <<= 1) bound = fmin(bound, __shfl_xor(bound, s, 64));
-    if (lane == 0) mins[threadIdx.x >> 6] = bound;
+    // every lane holds its wave's minimum; a workgroup of one wave fills all slots
+    if (lane < (blockDim.x == 64 ? 4 : 1)) mins[(threadIdx.x >> 6) + lane] = bound;
     __syncthreads();
     if (threadIdx.x == 0)
       atomicMin(&lp.bounds[blockIdx.x % lp.slots], ordered_key(fmin(fmin(mins[0], mins[1]), fmin(mins[2], mins[3]))));
@@ -929,9 +930,18 @@ static void go_force(const HydroArgs &a, int hg_mode, unsigned blocks, hipStream
   }
 }
 
+// Meshes of at most one wave per CU take a workgroup per wave, so that no two
+// waves share a CU's load path while others idle (EOS with the next forces:
+// 16^3 elements 6.3 -> 5.8 us, 24^3 6.45 -> 6.15); larger ones keep four waves
+// per workgroup, whose minimum is one atomic instead of four (40^3 7.25 us
+// against 8.6, 90^3 30 against 40).
+constexpr int64_t kSmallMesh = 256 * 64;
+static unsigned mesh_block(const HydroArgs &a) { return a.E <= kSmallMesh ? 64 : 256; }
+
 template <int NEXT>
 static void go_eos(const HydroArgs &a, const HydroLoop &lp, int eos_mode, hipStream_t s) {
-  const dim3 g((unsigned)((hydro_lanes(a.E, 1) + 255) / 256)), b(256);
+  const unsigned block = eos_mode == kEosTafBlock ? 256 : mesh_block(a);
+  const dim3 g((unsigned)((hydro_lanes(a.E, 1) + block - 1) / block)), b(block);
   switch (eos_mode) {
     case kEosExact: hipLaunchKernelGGL((k_hydro_eos<kEosExact, NEXT>), g, b, 0, s, a, lp); break;
     case kEosTafWave: hipLaunchKernelGGL((k_hydro_eos<kEosTafWave, NEXT>), g, b, 0, s, a, lp); break;
@@ -943,12 +953,12 @@ static void go_eos(const HydroArgs &a, const HydroLoop &lp, int eos_mode, hipStr
 }
 
 hipError_t launch_hydro_step(const HydroArgs &a, int hg_mode, int eos_mode, hipStream_t s) {
-  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256), nblocks = (unsigned)((a.Nn + 255) / 256);
+  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256), nblocks = (unsigned)((a.Nn + mesh_block(a) - 1) / mesh_block(a));
   HydroLoop lp = {};
   lp.dt = &a.clock[1];
   go_force(a, step_hg_mode(a, hg_mode), fblocks, s);
   hipLaunchKernelGGL(k_hydro_dt, dim3(1), dim3(256), 0, s, a, (int64_t)fblocks, lp);
-  hipLaunchKernelGGL(k_hydro_node<false>, dim3(nblocks), dim3(256), 0, s, a, lp);
+  hipLaunchKernelGGL(k_hydro_node<false>, dim3(nblocks), dim3(mesh_block(a)), 0, s, a, lp);
   go_eos<kNoNext>(a, lp, eos_mode, s);
   return hipGetLastError();
 }
@@ -982,7 +992,7 @@ hipError_t launch_hydro_run(HydroArgs a, int hg_mode, int eos_mode, int steps, h
     }
     return hipSuccess;
   }
-  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256), nblocks = (unsigned)((a.Nn + 255) / 256);
+  const unsigned fblocks = (unsigned)((a.hg_L + 255) / 256), nblocks = (unsigned)((a.Nn + mesh_block(a) - 1) / mesh_block(a));
   const int slots = (int)((parts - 1) / 2 < 64 ? (parts - 1) / 2 : 64);
   unsigned long long *const set[2] = {(unsigned long long *)a.dt_partials, (unsigned long long *)a.dt_partials + slots};
   double *const cell[2] = {&a.clock[1], a.dt_partials + 2 * slots};
@@ -992,7 +1002,7 @@ hipError_t launch_hydro_run(HydroArgs a, int hg_mode, int eos_mode, int steps, h
   lp.bounds_next = set[1];
   go_force(a, step_hg_mode(a, hg_mode), fblocks, s);
   hipLaunchKernelGGL(k_hydro_dt, dim3(1), dim3(256), 0, s, a, (int64_t)fblocks, lp);
-  hipLaunchKernelGGL(k_hydro_node<false>, dim3(nblocks), dim3(256), 0, s, a, lp);
+  hipLaunchKernelGGL(k_hydro_node<false>, dim3(nblocks), dim3(mesh_block(a)), 0, s, a, lp);
   for (int k = 0; k + 1 < steps; ++k) {
     // step k's EOS and step k + 1's forces
     lp.dt = cell[k & 1];
@@ -1008,7 +1018,7 @@ hipError_t launch_hydro_run(HydroArgs a, int hg_mode, int eos_mode, int steps, h
     lp.dt_prev = cell[k & 1];
     lp.dt = cell[(k + 1) & 1];
     lp.bounds_next = set[k & 1];
-    hipLaunchKernelGGL(k_hydro_node<true>, dim3(nblocks), dim3(256), 0, s, a, lp);
+    hipLaunchKernelGGL(k_hydro_node<true>, dim3(nblocks), dim3(mesh_block(a)), 0, s, a, lp);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -462,3 +462,12 @@ def test_loop_of_steps_equals_single_steps_at_slot_edges(n, tech):
             if va is not None:
                 assert np.array_equal(va, gb[f]), (k, f)
     assert int(a.status.item()) == 0
+
+
+@pytest.mark.parametrize("n", [25, 26])
+@pytest.mark.parametrize("tech", [Tech(), Tech(eos=(2, 2, 0.01, "thread")), Tech(eos=(2, 3, 0.01, "wave"))],
+                         ids=["exact", "eos_thread", "eos_wave"])
+def test_loop_of_steps_equals_single_steps_at_the_workgroup_edge(n, tech):
+    """25^3 elements are the largest mesh with a workgroup per wave, 26^3 the
+    smallest with four waves in one."""
+    test_loop_of_steps_equals_single_steps_at_slot_edges(n, tech)
