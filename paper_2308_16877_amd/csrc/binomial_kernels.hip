@@ -105,6 +105,7 @@ struct BoHead {
   float call, put;   // European prices, where `sums` says so
   int sums;          // bit 0: the call is final, bit 1: the put is
   int regular;       // 0 < p < 1, prices positive and finite
+  int put_exp;       // 2^put_exp is at least e^{-r T}; 0 where r >= 0
 };
 
 // The tree's parameters and, with `sums`, its European call and put as what
@@ -134,7 +135,8 @@ __device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T,
   const double p = (a - d) / (u - d), q = 1.0 - p, l2u = su * kLog2eD;
   const int C = (N + 64) >> 6;
   const int j0 = lane * C;
-  BoHead h{u, d, l2u, p * disc, q * disc, (double)Sf * exp2((double)(2 * j0 - N) * l2u), 0.0f, 0.0f, 0, 0};
+  const int put_exp = r < 0.0f ? (int)ceil(fmin(-(double)N * rdt * kLog2eD, 4096.0)) : 0;
+  BoHead h{u, d, l2u, p * disc, q * disc, (double)Sf * exp2((double)(2 * j0 - N) * l2u), 0.0f, 0.0f, 0, 0, put_exp};
   h.regular = uniform(p > 0.0 && q > 0.0 && Sf > 0.0f && Kf > 0.0f && Sf < INFINITY && Kf < INFINITY);
   if (sums) {
     if (h.regular)
@@ -269,23 +271,28 @@ __device__ __forceinline__ int fresh_lane() {
 // A = V - e >= 0, V = max(continuation, e) becomes
 //   A = max(pu A_up + pd A_dn + D, 0),  D = pu e_up + pd e_dn - e,
 // with A = 0 on the leaves.  D depends on the position alone and is formed
-// once, in FP64.  Scaled by a power of two not below K (A <= K: a put is
-// worth at most K, a call at most its spot) the maximum is the clamp of the
-// second multiply-add, so a node costs two instructions; max itself would be
-// a third, and one that issues at half the rate of a multiply-add.  The
+// once, in FP64.  Scaled by a power of two not below A's largest value the
+// maximum is the clamp of the second multiply-add, so a node costs two
+// instructions; max itself would be a third, and one that issues at half the
+// rate of a multiply-add.  That value is at most K for a call, which is worth
+// at most its spot at any rate, and for a put at r >= 0; at r < 0 a put is
+// worth up to K e^{|r| T}, and its scale is larger by that (put_exp).  The
 // rounding errors are those of the premium, not of the price, and D is an
-// exact zero where the option is out of the money.  NV = 2: call (value 0) and put.
+// exact zero where the option is out of the money.  NV = 2: call (value 0) and
+// put; NV = 1, longer trees: the one whose European price is not its own, so a
+// put at r > 0 only.
 template <int CM, int NV>
 __device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, int N, float sgn, LdsFloat *lds,
                                            float (&price)[NV]) {
   const int lane = fresh_lane();
   const int need = (N + 64) >> 6;
-  const int ks = __builtin_amdgcn_frexp_expf(Kf);  // K <= 2^ks
+  const int kexp = __builtin_amdgcn_frexp_expf(Kf);  // K <= 2^kexp
   float A[NV][CM], D0[NV][CM], D1[NV][CM];
   const double K = (double)Kf, u2 = q.u * q.u;
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const double sg = NV == 2 ? (v == 0 ? 1.0 : -1.0) : (double)sgn;
+    const int ks = kexp + (NV == 2 && v == 1 ? q.put_exp : 0);
     auto ex = [&](double x) { return fmax(sg * (x - K), 0.0); };
     double X = q.X;
     double below = ex(X * q.d), e = ex(X);  // at the odd position below, at this even position
@@ -316,7 +323,7 @@ __device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, 
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const float sg = NV == 2 ? (v == 0 ? 1.0f : -1.0f) : sgn;
-    price[v] = ldexpf(root[v], ks) + fmaxf(sg * (Sf - Kf), 0.0f);
+    price[v] = ldexpf(root[v], kexp + (NV == 2 && v == 1 ? q.put_exp : 0)) + fmaxf(sg * (Sf - Kf), 0.0f);
   }
 }
 

@@ -279,3 +279,27 @@ def test_tree_with_probability_above_one(steps, american):
     ref, scale = oracle_values(x, steps, american)
     assert np.all(np.isfinite(ref))
     assert np.all(np.abs(y - ref) <= 3.0 * tol(steps) * np.maximum(scale, np.abs(ref)))
+
+
+@pytest.mark.parametrize("steps", [1, 2, 63, 64, 100, 126, 127, 128, 300])
+@pytest.mark.parametrize("american", [True, False])
+def test_deep_puts_at_negative_rates(steps, american):
+    """At r < 0 a put is worth up to K e^{|r| T}, more than its strike:
+    |r| T up to 6 on strikes just below, at and above powers of two, wherever
+    0 < p < 1.  The positive, discount-weighted averages keep the error
+    linear in N of the scale S + K e^{-rT}, as at r >= 0."""
+    rows = [(S, K, T, r, v) for S in (0.5, 20.0, 100.0) for K in (30.0, 63.9, 64.0, 100.0, 127.0)
+            for T in (1.0, 10.0, 20.0, 30.0) for r in (-0.2, -0.1, -0.05, -0.03) for v in (0.2, 0.3, 1.5)]
+    x = np.array(rows, np.float32).T
+    dt = x[2].astype(np.float64) / steps
+    x = np.ascontiguousarray(x[:, np.abs(x[3]) * np.sqrt(dt) < 0.9 * x[4]])  # 0 < p < 1
+    assert x.shape[1] >= 100 and np.max(-x[3] * x[2]) > np.log(3.0)
+    ref, scale = oracle_values(x, steps, american)
+    assert np.any(ref[1] > 1.5 * x[1])
+    y, _, _ = run(hpac.hpac_bo_exact, x, steps, 1, trace=False, counters=False, american=american)
+    assert np.all(np.abs(y - ref) <= tol(steps) * scale)
+    for fn, kw in ((hpac.hpac_bo_iact, dict(table_size=4, threshold=0.0)),
+                   (hpac.hpac_bo_taf, dict(history_size=2, prediction_size=2, rsd_threshold=0.0)),
+                   (hpac.hpac_bo_perfo, dict(kind="small", param=0))):
+        z, _, _ = run(fn, x, steps, 3, american=american, **kw)
+        assert np.array_equal(z, y)
