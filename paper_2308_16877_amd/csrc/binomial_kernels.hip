@@ -353,13 +353,17 @@ __device__ __forceinline__ void bo_values(const BoHead &q, float S, float K, int
     E1[0][c] = american ? x1 : __builtin_nanf("");
     asm volatile("" : "+v"(E0[0][c]), "+v"(E1[0][c]));  // one position after the other, as above
   }
-  // max(cont, e) as a median with +inf, one instruction: fmaxf would first
-  // quiet e, a register from outside the loop, with a second one.  Like
-  // fmaxf it returns the other operand when one is NaN.
-  float inf = INFINITY;
-  asm("" : "+v"(inf));
+  // max(cont, e) as the instruction itself: fmaxf would first quiet e, a
+  // register from outside the loop, with a second one.  Like fmaxf it returns
+  // the other operand when one is NaN, and NaN when both are.
   auto node = [&](int v, float e, float up, float dn) {
-    return __builtin_amdgcn_fmed3f(__builtin_fmaf(pu, up, pd * dn), v ? -e : e, inf);
+    const float cont = __builtin_fmaf(pu, up, pd * dn);
+    float x;
+    if (v)
+      asm("v_max_f32_e64 %0, %1, -%2" : "=v"(x) : "v"(cont), "v"(e));
+    else
+      asm("v_max_f32_e32 %0, %1, %2" : "=v"(x) : "v"(cont), "v"(e));
+    return x;
   };
   bo_walk<CM, NV, 1>(N, lane, lds, V, E0, E1, node, price);
 }

@@ -303,3 +303,22 @@ def test_deep_puts_at_negative_rates(steps, american):
                    (hpac.hpac_bo_perfo, dict(kind="small", param=0))):
         z, _, _ = run(fn, x, steps, 3, american=american, **kw)
         assert np.array_equal(z, y)
+
+
+@pytest.mark.parametrize("steps", [1, 2, 63, 64, 127, 128, 300])
+@pytest.mark.parametrize("american", [True, False])
+def test_undefined_prices_are_nan(steps, american):
+    """A NaN time, rate or volatility, a negative time and a tree without an
+    up-move leave no defined continuation: NaN for European options; American
+    ones keep their exercise value, or NaN where that is undefined too."""
+    nan = float("nan")
+    rows = [(20, 25, nan, 0.02, 0.3), (20, 25, 1, nan, 0.3), (20, 25, 1, 0.02, nan), (20, 25, -1, 0.02, 0.3),
+            (20, 25, 0, 0.02, 0.3), (20, 25, 1, 0.02, 0), (30, 25, 1, nan, 0.3), (nan, 25, 1, nan, 0.3),
+            (20, nan, 1, nan, 0.3), (20, 25, 1, 0.02, 0.3)]
+    x = np.ascontiguousarray(np.array(rows, np.float32).T)
+    ref, _ = oracle_values(x, steps, american)
+    assert american or np.all(np.isnan(ref[:, :-1]))
+    y, _, _ = run(hpac.hpac_bo_exact, x, steps, 1, trace=False, counters=False, american=american)
+    assert np.array_equal(np.isnan(y), np.isnan(ref))
+    known = ~np.isnan(ref)
+    assert np.all(np.abs(y - ref)[known] <= tol(steps) * 45.0)
