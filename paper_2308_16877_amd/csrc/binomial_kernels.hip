@@ -337,10 +337,10 @@ __device__ __forceinline__ void bo_values(const BoHead &q, float S, float K, int
   const int need = (N + 64) >> 6;
   const float pu = (float)q.pu, pd = (float)q.pd, l2u = (float)q.l2u, l2ul = (float)(q.l2u - (double)l2u);
   float V[NV][CM], E0[1][CM], E1[1][CM];  // exercise values, NaN (no exercise) for European options
-  // S u^k, the exponent's rounding error carried into the result
+  // S u^k, the exponent's rounding error carried into the result where it has one
   auto spot = [&](int k) {
     const float f = (float)k, h = f * l2u;
-    const float e = __builtin_fmaf(f, l2ul, __builtin_fmaf(f, l2u, -h));
+    const float e = fabsf(h) < INFINITY ? __builtin_fmaf(f, l2ul, __builtin_fmaf(f, l2u, -h)) : 0.0f;
     return S * (__builtin_amdgcn_exp2f(h) * __builtin_fmaf(e, 0.693147180559945309f, 1.0f));
   };
 #pragma unroll

@@ -322,3 +322,19 @@ def test_undefined_prices_are_nan(steps, american):
     assert np.array_equal(np.isnan(y), np.isnan(ref))
     known = ~np.isnan(ref)
     assert np.all(np.abs(y - ref)[known] <= tol(steps) * 45.0)
+
+
+@pytest.mark.parametrize("steps", [1, 3, 64, 127, 128, 301])
+@pytest.mark.parametrize("american", [True, False])
+def test_put_of_unbounded_volatility(steps, american):
+    """v = inf: every leaf but the highest is worthless, so a put is worth its
+    discounted strike (American: at least one step's discount, and the better
+    of the two); the call has no defined price."""
+    x = np.ascontiguousarray(np.array([(20, 25, 1, r, np.inf) for r in (-0.1, 0.0, 0.02, 0.5)], np.float32).T)
+    y, _, _ = run(hpac.hpac_bo_exact, x, steps, 1, trace=False, counters=False, american=american)
+    K, T, r = (x[j].astype(np.float64) for j in (1, 2, 3))
+    want = K * np.exp(-r * T)
+    if american:  # exercised one step from now, unless waiting is worth more
+        want = np.maximum(want, K * np.exp(-r * T / steps))
+    assert np.all(np.abs(y[1] - want) <= tol(steps) * (20.0 + want))
+    assert np.all(np.isnan(y[0])) or american
