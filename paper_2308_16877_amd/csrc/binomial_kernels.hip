@@ -120,8 +120,10 @@ struct BoHead {
 // pu (X u - K) + pd (X d - K) = X - K / a, so for r >= 0 a call is never
 // exercised before its expiry, and with the signs turned a put never for
 // r <= 0: such a price is the European one.  Irregular parameters (p outside
-// (0, 1), prices that are not positive and finite) leave both values to the
-// induction.
+// (0, 1), prices that are not positive and finite, exponents out of range)
+// leave both values to the induction.  Where the highest leaves' spots leave
+// FP64's range (v sqrt(T N) above 600) the call is summed on weighted spots,
+// which do not.
 //
 // A function of its own: inlined, the FP64 constants and temporaries are kept
 // in registers across the caller's option loop (over 200 VGPRs).
@@ -137,7 +139,10 @@ __device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T,
   const int j0 = lane * C;
   const int put_exp = r < 0.0f ? (int)ceil(fmin(-(double)N * rdt * kLog2eD, 4096.0)) : 0;
   BoHead h{u, d, l2u, p * disc, q * disc, (double)Sf * exp2((double)(2 * j0 - N) * l2u), 0.0f, 0.0f, 0, 0, put_exp};
-  h.regular = uniform(p > 0.0 && q > 0.0 && Sf > 0.0f && Kf > 0.0f && Sf < INFINITY && Kf < INFINITY);
+  // the last two: K e^{-r T} is finite, and a lane's spots, of at most 16
+  // leaves, do not run from zero or infinity to a price that counts
+  h.regular = uniform(p > 0.0 && q > 0.0 && Sf > 0.0f && Kf > 0.0f && Sf < INFINITY && Kf < INFINITY &&
+                      fabs((double)N * rdt) < 700.0 && fabs((double)C * su) < 300.0);
   if (sums) {
     if (h.regular)
       h.sums = (uniform(!american || r >= 0.0f) ? 1 : 0) | (uniform(!american || r <= 0.0f) ? 2 : 0);
@@ -155,7 +160,8 @@ __device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T,
       const double before = wave_scan_add(own) - own;
       const double l2 = log2(lane == 0 ? p : q);
       const double l2p = read_lane(l2, 0), l2q = read_lane(l2, 1);
-      double w = exp2(before + (double)j0 * l2p + (double)(N - j0) * l2q - (double)N * rdt * kLog2eD);
+      const double l2w = before + (double)j0 * l2p + (double)(N - j0) * l2q - (double)N * rdt * kLog2eD;
+      double w = exp2(l2w);
       double X = h.X;
       const double u2 = u * u, K = (double)Kf, pq = p / q;
       double call = 0.0, put = 0.0;
@@ -168,6 +174,21 @@ __device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T,
         }
         w *= pq * ((double)(N - j) / (double)(j + 1));
         X *= u2;
+      }
+      if (!uniform(fabs((double)N * su) < 600.0)) {
+        const double l2s = log2((double)Sf) + (double)(2 * j0 - N) * l2u;
+        double l2x = l2s - log2(K), wx = exp2(l2w + l2s);
+        w = exp2(l2w);
+        call = 0.0;
+#pragma unroll 1
+        for (int c = 0; c < C; ++c) {
+          const int j = j0 + c;
+          if (j <= N && l2x > 0.0) call += wx - K * w;
+          const double next = pq * ((double)(N - j) / (double)(j + 1));
+          wx *= next * u2;
+          w *= next;
+          l2x += 2.0 * l2u;
+        }
       }
       h.call = (float)read_lane(wave_scan_add(call), 63);
       h.put = (float)read_lane(wave_scan_add(put), 63);

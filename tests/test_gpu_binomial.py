@@ -338,3 +338,45 @@ def test_put_of_unbounded_volatility(steps, american):
         want = np.maximum(want, K * np.exp(-r * T / steps))
     assert np.all(np.abs(y[1] - want) <= tol(steps) * (20.0 + want))
     assert np.all(np.isnan(y[0])) or american
+
+
+@pytest.mark.parametrize("steps", [63, 64, 127, 128, 300, 1000])
+@pytest.mark.parametrize("american", [True, False])
+def test_spots_beyond_the_range_of_floats(steps, american):
+    """Volatilities at which the highest leaves' spots leave FP32's and FP64's
+    range.  The call is worth about its spot: against the sum over the leaves
+    in log space, the put too where it is the European one.  Both stay within
+    what a put and a call can be worth."""
+    from scipy.special import gammaln
+    rows = [(S, K, T, r, v) for S in (20.0, 1e4) for K in (5.0, 25.0, 63.9, 1e30) for T in (1.0, 30.0)
+            for r in (-0.1, 0.0, 0.02, 0.5) for v in (5.0, 20.0, 100.0)]
+    x = np.ascontiguousarray(np.array(rows, np.float32).T)
+    S, K, T, r, v = (c.astype(np.float64)[None, :] for c in x)
+    su, a = v * np.sqrt(T / steps), r * T / steps
+    with np.errstate(over="ignore"):
+        u, d = np.exp(su), np.exp(-su)
+        p = (np.exp(a) - d) / (u - d)
+    i = np.arange(steps + 1)[:, None]
+    lw = (gammaln(steps + 1) - gammaln(i + 1) - gammaln(steps - i + 1) + i * np.log(p) + (steps - i) * np.log1p(-p)
+          - steps * a)
+    lx = np.log(S) + (2 * i - steps) * su
+    itm = lx > np.log(K)
+    with np.errstate(over="ignore"):
+        call = np.sum(np.where(itm, np.exp(lw + lx) - K * np.exp(lw), 0.0), axis=0)
+        put = np.sum(np.where(itm, 0.0, np.exp(lw) * (K - np.exp(np.minimum(lx, 700.0)))), axis=0)
+    y, _, _ = run(hpac.hpac_bo_exact, x, steps, 1, trace=False, counters=False, american=american)
+    scale = (S + K * np.exp(-r * T))[0]
+    summed = steps >= (128 if american else 64)  # smaller trees: an induction in FP32, inf where its spots are
+    for o, ref, same in ((0, call, x[3] >= 0), (1, put, x[3] <= 0)):
+        ok = np.abs(y[o] - ref) <= tol(steps) * scale
+        if not american:
+            assert np.all(ok) if summed else np.all(ok | np.isinf(y[o]))
+        elif summed:
+            assert np.all(ok[same])
+    if summed:  # a call's scale is its spot, whatever the strike
+        near = np.abs(y[0] - call) <= 64 * tol(steps) * x[0]
+        assert np.all(near[x[3] >= 0] if american else near)
+    if american and summed:
+        most = np.maximum(K, K * np.exp(-r * T))[0]  # exercised at once on a worthless spot, or held
+        assert np.all(y[0] <= x[0] * (1 + tol(steps))) and np.all(y[1] <= most * (1 + tol(steps)))
+        assert np.all(y[0] >= x[0] - x[1]) and np.all(y[1] >= x[1] - x[0])
