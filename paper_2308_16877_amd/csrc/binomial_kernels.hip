@@ -86,7 +86,28 @@ __device__ __forceinline__ double wave_scan_add(double v) {
   return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
 }
 
-constexpr double kLog2eD = 1.4426950408889634074;
+constexpr double kLog2eD = 1.4426950408889634074, kLn2D = 0.69314718055994530942;
+
+// 2^x as m 2^e, m in [2^-1/2, 2^1/2], whatever the size of x: m by the Taylor
+// series of e^t, |t| <= ln 2 / 2, to t^13 / 13! (the next term is below 5e-18).
+struct Power2 {
+  double m;
+  int e;
+  __device__ __forceinline__ explicit Power2(double x) {
+    const double n = rint(x), t = (x - n) * kLn2D;
+    double s = 1.0 / 6227020800.0;
+    constexpr double kFact[13] = {1.0, 1.0, 2.0, 6.0, 24.0, 120.0, 720.0, 5040.0, 40320.0, 362880.0, 3628800.0,
+                                  39916800.0, 479001600.0};
+#pragma unroll
+    for (int k = 12; k >= 0; --k) {
+      double c = 1.0 / kFact[k];
+      asm("" : "+s"(c));  // an operand in scalar registers, not moved to vector ones first
+      s = __builtin_fma(s, t, c);
+    }
+    m = s;
+    e = (int)n;
+  }
+};
 
 struct BoOut {
   float call, put;
@@ -97,7 +118,9 @@ typedef __attribute__((address_space(3))) float LdsFloat;
 __device__ __forceinline__ bool uniform(bool b) { return __builtin_amdgcn_readfirstlane((int)b) != 0; }
 
 // What the FP64 part of a price hands on: the tree's FP32 parameters and the
-// prices that need no induction.
+// prices that need no induction.  16 dwords, the most that a function returns
+// in registers: a 17th sends it through scratch memory, and 65,536 American
+// options on 8 steps take 62 us instead of 33.
 struct BoHead {
   double u, d, l2u;  // up and down factors, log2 u
   double pu, pd;     // discounted probabilities
@@ -105,8 +128,8 @@ struct BoHead {
   float call, put;   // European prices, where `sums` says so
   int sums;          // bit 0: the call is final, bit 1: the put is
   int regular;       // 0 < p < 1, prices positive and finite
-  int put_exp;       // 2^put_exp is at least e^{-r T}; 0 where r >= 0
 };
+static_assert(sizeof(BoHead) <= 64, "returned in registers");
 
 // The tree's parameters and, with `sums`, its European call and put as what
 // they are: the discounted expectation of the payoff over the leaves, whose
@@ -120,10 +143,8 @@ struct BoHead {
 // pu (X u - K) + pd (X d - K) = X - K / a, so for r >= 0 a call is never
 // exercised before its expiry, and with the signs turned a put never for
 // r <= 0: such a price is the European one.  Irregular parameters (p outside
-// (0, 1), prices that are not positive and finite, exponents out of range)
-// leave both values to the induction.  Where the highest leaves' spots leave
-// FP64's range (v sqrt(T N) above 600) the call is summed on weighted spots,
-// which do not.
+// (0, 1), prices that are not positive and finite, u above e^{300 / C}) leave
+// both values to the induction.
 //
 // A function of its own: inlined, the FP64 constants and temporaries are kept
 // in registers across the caller's option loop (over 200 VGPRs).
@@ -137,12 +158,12 @@ __device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T,
   const double p = (a - d) / (u - d), q = 1.0 - p, l2u = su * kLog2eD;
   const int C = (N + 64) >> 6;
   const int j0 = lane * C;
-  const int put_exp = r < 0.0f ? (int)ceil(fmin(-(double)N * rdt * kLog2eD, 4096.0)) : 0;
-  BoHead h{u, d, l2u, p * disc, q * disc, (double)Sf * exp2((double)(2 * j0 - N) * l2u), 0.0f, 0.0f, 0, 0, put_exp};
-  // the last two: K e^{-r T} is finite, and a lane's spots, of at most 16
-  // leaves, do not run from zero or infinity to a price that counts
+  const Power2 x((double)(2 * j0 - N) * l2u);  // the lane's first spot, over S
+  BoHead h{u, d, l2u, p * disc, q * disc, ldexp((double)Sf * x.m, x.e), 0.0f, 0.0f, 0, 0};
+  // the last one: a lane's weights and spots, of at most 16 leaves, do not run
+  // from zero or infinity to a value that counts
   h.regular = uniform(p > 0.0 && q > 0.0 && Sf > 0.0f && Kf > 0.0f && Sf < INFINITY && Kf < INFINITY &&
-                      fabs((double)N * rdt) < 700.0 && fabs((double)C * su) < 300.0);
+                      fabs((double)C * su) < 300.0);
   if (sums) {
     if (h.regular)
       h.sums = (uniform(!american || r >= 0.0f) ? 1 : 0) | (uniform(!american || r <= 0.0f) ? 2 : 0);
@@ -160,36 +181,32 @@ __device__ __attribute__((noinline)) BoHead bo_head(float Sf, float Kf, float T,
       const double before = wave_scan_add(own) - own;
       const double l2 = log2(lane == 0 ? p : q);
       const double l2p = read_lane(l2, 0), l2q = read_lane(l2, 1);
-      const double l2w = before + (double)j0 * l2p + (double)(N - j0) * l2q - (double)N * rdt * kLog2eD;
-      double w = exp2(l2w);
-      double X = h.X;
+      const Power2 f(before + (double)j0 * l2p + (double)(N - j0) * l2q - (double)N * rdt * kLog2eD);
+      double w = ldexp(f.m, f.e);
       const double u2 = u * u, K = (double)Kf, pq = p / q;
       double call = 0.0, put = 0.0;
-#pragma unroll 1
-      for (int c = 0; c < C; ++c) {
-        const int j = j0 + c;
-        if (j <= N) {
-          call += w * fmax(X - K, 0.0);
-          put += w * fmax(K - X, 0.0);
-        }
-        w *= pq * ((double)(N - j) / (double)(j + 1));
-        X *= u2;
-      }
-      if (!uniform(fabs((double)N * su) < 600.0)) {
-        const double l2s = log2((double)Sf) + (double)(2 * j0 - N) * l2u;
-        double l2x = l2s - log2(K), wx = exp2(l2w + l2s);
-        w = exp2(l2w);
-        call = 0.0;
+      // far: the spots leave FP64's range, and their products with the weights,
+      // which do not, take their place (a multiplication more per leaf: with
+      // it throughout, 65,536 European options on 512 steps take 103 us, not 99)
+      auto leaves = [&](auto far_tag) {
+        constexpr bool kFar = decltype(far_tag)::value;
+        double X = kFar ? ldexp((double)Sf * (f.m * x.m), f.e + x.e) : h.X;
 #pragma unroll 1
         for (int c = 0; c < C; ++c) {
           const int j = j0 + c;
-          if (j <= N && l2x > 0.0) call += wx - K * w;
+          if (j <= N) {
+            call += kFar ? fmax(X - K * w, 0.0) : w * fmax(X - K, 0.0);
+            put += kFar ? fmax(K * w - X, 0.0) : w * fmax(K - X, 0.0);
+          }
           const double next = pq * ((double)(N - j) / (double)(j + 1));
-          wx *= next * u2;
           w *= next;
-          l2x += 2.0 * l2u;
+          X *= kFar ? next * u2 : u2;
         }
-      }
+      };
+      if (uniform(fabs((double)N * su) < 500.0))
+        leaves(std::false_type{});
+      else
+        leaves(std::true_type{});
       h.call = (float)read_lane(wave_scan_add(call), 63);
       h.put = (float)read_lane(wave_scan_add(put), 63);
       if (american) {  // never below the exercise value, rounding included
@@ -303,8 +320,8 @@ __device__ __forceinline__ int fresh_lane() {
 // put; NV = 1, longer trees: the one whose European price is not its own, so a
 // put at r > 0 only.
 template <int CM, int NV>
-__device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, int N, float sgn, LdsFloat *lds,
-                                           float (&price)[NV]) {
+__device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, int N, float sgn, int put_exp,
+                                           LdsFloat *lds, float (&price)[NV]) {
   const int lane = fresh_lane();
   const int need = (N + 64) >> 6;
   const int kexp = __builtin_amdgcn_frexp_expf(Kf);  // K <= 2^kexp
@@ -313,7 +330,7 @@ __device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, 
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const double sg = NV == 2 ? (v == 0 ? 1.0 : -1.0) : (double)sgn;
-    const int ks = kexp + (NV == 2 && v == 1 ? q.put_exp : 0);
+    const int ks = kexp + (NV == 2 && v == 1 ? put_exp : 0);
     auto ex = [&](double x) { return fmax(sg * (x - K), 0.0); };
     double X = q.X;
     double below = ex(X * q.d), e = ex(X);  // at the odd position below, at this even position
@@ -344,7 +361,7 @@ __device__ __forceinline__ void bo_premium(const BoHead &q, float Sf, float Kf, 
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const float sg = NV == 2 ? (v == 0 ? 1.0f : -1.0f) : sgn;
-    price[v] = ldexpf(root[v], kexp + (NV == 2 && v == 1 ? q.put_exp : 0)) + fmaxf(sg * (Sf - Kf), 0.0f);
+    price[v] = ldexpf(root[v], kexp + (NV == 2 && v == 1 ? put_exp : 0)) + fmaxf(sg * (Sf - Kf), 0.0f);
   }
 }
 
@@ -356,12 +373,14 @@ __device__ __forceinline__ void bo_values(const BoHead &q, float S, float K, int
                                           LdsFloat *lds, float (&price)[NV]) {
   const int lane = fresh_lane();
   const int need = (N + 64) >> 6;
-  const float pu = (float)q.pu, pd = (float)q.pd, l2u = (float)q.l2u, l2ul = (float)(q.l2u - (double)l2u);
+  const float pu = (float)q.pu, pd = (float)q.pd;
+  const float l2u = (float)q.l2u, l2ul = (float)(q.l2u - (double)l2u);
   float V[NV][CM], E0[1][CM], E1[1][CM];  // exercise values, NaN (no exercise) for European options
-  // S u^k, the exponent's rounding error carried into the result where it has one
+  // S u^k, the exponent's rounding error e carried into the result; where the
+  // exponent is infinite e is NaN, and some number takes its place
   auto spot = [&](int k) {
     const float f = (float)k, h = f * l2u;
-    const float e = fabsf(h) < INFINITY ? __builtin_fmaf(f, l2ul, __builtin_fmaf(f, l2u, -h)) : 0.0f;
+    const float e = __builtin_amdgcn_fmed3f(__builtin_fmaf(f, l2ul, __builtin_fmaf(f, l2u, -h)), -1.0f, 1.0f);
     return S * (__builtin_amdgcn_exp2f(h) * __builtin_fmaf(e, 0.693147180559945309f, 1.0f));
   };
 #pragma unroll
@@ -417,15 +436,18 @@ __device__ __forceinline__ BoOut bo_price(float S, float K, float T, float r, fl
   if (sums == 3) return o;
   if constexpr (CM <= 2) {
     float p[2];
-    if (american && regular)
-      bo_premium<CM, 2>(q, S, K, N, -1.0f, lds, p);
-    else
+    if (american && regular) {
+      int put_exp = 0;  // 2^put_exp is at least e^{-r T}
+      if (uniform(r < 0.0f)) put_exp = (int)ceil(fmin(-(double)r * (double)T * kLog2eD, 4096.0));
+      bo_premium<CM, 2>(q, S, K, N, -1.0f, put_exp, lds, p);
+    } else {
       bo_values<CM, 2>(q, S, K, N, american, 1.0f, lds, p);
+    }
     o = BoOut{p[0], p[1]};
   } else {
     if (!regular) return bo_irregular<CM>(q, S, K, N, american, lds);
     float p[1];
-    bo_premium<CM, 1>(q, S, K, N, sums == 1 ? -1.0f : 1.0f, lds, p);
+    bo_premium<CM, 1>(q, S, K, N, sums == 1 ? -1.0f : 1.0f, 0, lds, p);
     (sums == 1 ? o.put : o.call) = p[0];
   }
   return o;
