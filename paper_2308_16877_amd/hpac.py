@@ -435,8 +435,8 @@ def hpac_bs_vjp_ref(inputs, source, grad_call, grad_put, grad_in, n=None, stream
 
 
 def _floats(v):
-    """Five numbers as a C array (an array's elements converted at once)."""
-    return (ctypes.c_float * 5)(*map(float, v.tolist() if hasattr(v, "tolist") else v))
+    """Five numbers as a C array (a one-dimensional array's converted at once)."""
+    return (ctypes.c_float * 5)(*map(float, v.tolist() if getattr(v, "ndim", 0) == 1 else v))
 
 
 def hpac_surrogate(inputs, outputs, params, norm, box_lo, box_hi, queue, queue_count, stream=None, n=None):

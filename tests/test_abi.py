@@ -388,3 +388,17 @@ def test_column_and_buffer_checks_agree_with_the_general_checks(monkeypatch):
                     assert quick == _outcome(hpac._check_buf, t, need, kind, "buf"), (t, kind, need)
         if not isinstance(t, (str, np.ndarray)):
             assert _outcome(hpac._addrs, [t]) == _outcome(lambda: [hpac._addr(t)])
+
+
+def test_box_bounds_take_every_form_of_five_numbers():
+    import numpy as np
+    import torch
+    want = [5.0, 1.0, 0.25, 0.02, 0.5]
+    a = np.array(want)
+    forms = [want, tuple(want), iter(want), a, a.astype(np.float32), a.reshape(5, 1), torch.tensor(want),
+             torch.tensor(want).reshape(5, 1), torch.tensor(want, requires_grad=True), list(a), np.array(want, object)]
+    for v in forms:
+        assert np.allclose(list(hpac._floats(v)), want)
+    for v in (want + [1.0], a.reshape(1, 5), ["x"] * 5):
+        with pytest.raises((TypeError, ValueError, IndexError)):
+            hpac._floats(v)
