@@ -975,8 +975,13 @@ constexpr bool kMixed =
 // SIMDs are filled without it, and the steps evaluated for nothing show (votes
 // that fail / pass, at 16 items per lane and 2^14 lanes: 4.5 / 5.6 us against
 // 12.4 / 7.0; at 64 and 2^15: 13.3 / 21.9 against 45.1 / 18.2); with fewer steps
-// there is no chain to shorten (3 per lane: 4.3 us both).
-constexpr int kTeamFrom = 4;
+// there is no chain to shorten (3 per lane: 4.3 us both).  A window of one or
+// two outputs that keeps passing leaves little of the chain either.  One always
+// passes: never.  Two (FP32 body, votes that fail / pass): 4 per lane and 1024
+// waves 3.3 / 3.7 us here, 4.2 / 3.4 there; 20 per lane and 256 waves 5.2 / 6.9
+// against 14.2 / 6.6, 24 per lane 7.6 both where they pass.  Three: 4 per lane
+// and 1024 waves 3.3 / 3.7 against 4.2 / 3.8.
+constexpr int team_from(int history) { return history >= 3 ? 4 : 24; }
 constexpr int64_t kTeamLanes = 1 << 14;
 
 struct ExactL {
@@ -1120,8 +1125,8 @@ hipError_t launch_iact(const LaunchCfg &c, const KArgs &a, int level, int table_
 template <class R, int LEVEL, int H>
 static void taf_go(const LaunchCfg &c, const KArgs &a, int p, float thr, float *st) {
   if constexpr (LEVEL == kWaveLvl) {
-    if constexpr (!kMixed<R> && R::kOut <= 2)
-      if (!st && !a.trace && !a.counters && a.ipt >= kTeamFrom && a.L <= kTeamLanes) {
+    if constexpr (!kMixed<R> && R::kOut <= 2 && H >= 2)
+      if (!st && !a.trace && !a.counters && a.ipt >= team_from(H) && a.L <= kTeamLanes) {
         hipLaunchKernelGGL((k_taf_team<R, H>), dim3((unsigned)(a.L / kWave)), dim3(kWave * kTeam), 0, c.stream, a, p,
                            thr);
         return;
