@@ -640,3 +640,25 @@ def test_taf_teams_equal_single_waves(dtype, region, h, p, theta):
         hpac.hpac_taf(cols, got, **kw)
         for a, b in zip(got, want):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), (n, ipt)
+
+
+def test_taf_longest_prediction_is_carried_across_launches():
+    # with a state, what is left of a prediction of the type's maximum covers
+    # the launches that follow, as one that just covers their steps does
+    n, ipt, launches = 64 * 9 * 3, 9, 4
+    x = [torch.full((n,), float(v), device=DEV) for v in (20.0, 25.0, 1.0, 0.02, 0.3)]
+    later = [c * 1.5 for c in x]  # read by accurate steps only, of which there are none after the vote
+    got = []
+    for p in (2 ** 31 - 1, 2 ** 31 - 2 - ipt, ipt * launches):
+        state = torch.zeros(hpac.hpac_taf_state_bytes(hpac.REGION_BS_PRICE, n, ipt, 2), dtype=torch.uint8, device=DEV)
+        outs = []
+        for k in range(launches):
+            out = [torch.full((n,), SENTINEL, device=DEV) for _ in range(2)]
+            trace = torch.zeros(hpac.hpac_trace_entries(n, ipt), dtype=torch.int32, device=DEV)
+            hpac.hpac_taf(later if k else x, out, history_size=2, prediction_size=p, rsd_threshold=0.01,
+                          items_per_lane=ipt, trace=trace, state=state)
+            outs += out + [trace]
+        got.append(outs)
+    for g in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], g))
+    assert all(torch.equal(got[0][3 * k + o], got[0][o]) for k in range(launches) for o in range(2))
