@@ -953,7 +953,12 @@ constexpr int64_t kMaxGridYZ = 65535;
 
 // Items per lane of k_exact_run and the batch from which it is taken: below,
 // half as many waves leave the chip less to overlap (FP16 body, 4.2M items:
-// 13.4 us against 12.6 with one item per lane; 6M: 20.0 against 22.3).
+// 13.4 us against 12.6 with one item per lane; columns not read lately, 6M
+// items: 19.4 against 21.2, 2^24: 47.3 against 54.4).  A batch that lies in the
+// last-level cache, as in a loop over the same columns, is the price of that:
+// 17.3 against 16.0 and 40.3 against 38.2.  FP32 body on BF16 columns: 2^24
+// items 43.2 against 54.3 and, from that cache, 41 both; BF16 body, bound by
+// its arithmetic: 88.1 against 88.6.
 constexpr int kRunItems = 2;
 constexpr int64_t kRunFrom = 5 << 20;
 // FP32 batches of this range keep the caller's items per lane: there the
@@ -965,8 +970,9 @@ constexpr int64_t kRunFrom = 5 << 20;
 constexpr int64_t kStridedFrom = 5 << 19, kStridedTo = 7 << 20, kStridedMixed = 3 << 22;
 
 // The FP32 body on FP16 columns: the mixed-precision instructions it compiles
-// to round some results differently in each kernel, so it keeps to one kernel
-// per path.
+// to round some results of k_exact_run and k_taf_team differently (one unit in
+// the last place of 0.06% of the items) from k_exact's and k_taf_wave's, whose
+// forms, streamed, counted or not, agree; so it keeps to those.
 template <class R>
 constexpr bool kMixed =
     std::is_base_of<RegionBSPrice, R>::value && std::is_same<typename R::io::elem, _Float16>::value;

@@ -217,3 +217,23 @@ def test_exact_outputs_do_not_depend_on_items_per_lane(n):
     torch.cuda.synchronize()
     for y in ys[1:]:
         assert torch.equal(y[0], ys[0][0]) and torch.equal(y[1], ys[0][1])
+
+
+@pytest.mark.parametrize("n", [4097, 3 * (1 << 22) - 1, 3 * (1 << 22)])
+def test_mixed_outputs_do_not_depend_on_items_per_lane(n):
+    """The FP32 body on FP16 columns: one, four and sixteen items per lane,
+    with and without a trace, give the same outputs on either side of the batch
+    size from which the launch keeps the caller's mapping."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    lo, hi = (torch.tensor(v, device=DEV, dtype=torch.float32) for v in (inputs.BOX_LO, inputs.BOX_HI))
+    x = [(lo[j] + (hi[j] - lo[j]) * torch.rand(n, generator=g, device=DEV)).half() for j in range(5)]
+    ys = []
+    for ipt in (1, 4, 16):
+        for traced in (False, True):
+            y = [torch.full((n,), -7.0, dtype=torch.float16, device=DEV) for _ in range(2)]
+            trace = torch.zeros(hpac.hpac_trace_entries(n, ipt), dtype=torch.int32, device=DEV) if traced else None
+            hpac.hpac_exact(x, y, items_per_lane=ipt, trace=trace)
+            ys.append(y)
+    torch.cuda.synchronize()
+    for y in ys[1:]:
+        assert torch.equal(y[0], ys[0][0]) and torch.equal(y[1], ys[0][1])
