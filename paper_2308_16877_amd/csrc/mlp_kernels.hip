@@ -546,9 +546,24 @@ hipError_t launch_mlp_infer(const MlpArgs &a, hipStream_t stream) {
   return a.n <= (int64_t)cus * 64 ? infer_go<1>(a, resident, stream) : infer_go<4>(a, resident, stream);
 }
 
+// A dispatch's grid size is a 32-bit count of lanes: with 1024 of them per 64
+// items, larger batches (from 2^28 items, whose partials are 81 GB) take
+// several launches.
+constexpr int64_t kGradBlocks = 0xFFFFFFFFll / (64 * kGradWaves);
+
 hipError_t launch_mlp_grad(const MlpGradArgs &a, hipStream_t stream) {
-  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)((a.n + 63) / 64)), dim3(64 * kGradWaves), 0, stream, a);
-  return hipGetLastError();
+  for (int64_t b0 = 0; b0 * kNH < a.n; b0 += kGradBlocks) {
+    MlpGradArgs part = a;
+    part.n = a.n - b0 * kNH < kGradBlocks * kNH ? a.n - b0 * kNH : kGradBlocks * kNH;
+    for (int j = 0; j < 5; ++j) part.x[j] += b0 * kNH;
+    for (int o = 0; o < 2; ++o) part.t[o] += b0 * kNH;
+    part.grad_partials += b0 * kNumParams;
+    part.loss_partials += b0;
+    hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)((part.n + kNH - 1) / kNH)), dim3(64 * kGradWaves), 0, stream, part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_mlp_adam(const AdamArgs &a, hipStream_t stream) {

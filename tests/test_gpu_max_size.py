@@ -90,3 +90,35 @@ def test_techniques_past_2_31_items(big):
             steps = -(-N // L)
             kept_items = sum(min(L, N - k * L) for k in range(steps) if k % M != M - 1)
             assert c[0] == N and c[1] == N - kept_items
+
+
+def test_training_gradient_past_one_dispatch():
+    """A batch just past 2^28 items, whose workgroups have more lanes than one
+    dispatch holds: the partial gradients and losses at both ends and around
+    the last workgroup of the first dispatch are those of batches of these
+    items alone, bit for bit (each belongs to 64 items and no others)."""
+    from paper_2308_16877_amd import surrogate
+    n, pool, P = (1 << 28) + 64 * 3 + 5, 1 << 20, hpac.MLP_NUM_PARAMS
+    g = torch.Generator(device=DEV).manual_seed(3)
+    cols = [torch.rand(pool, generator=g, device=DEV).repeat(-(-n // pool))[:n] for _ in range(7)]
+    norm = hpac.make_norm(in_center=np.full(5, 0.5), in_scale=np.full(5, 2.0), out_mean=np.array([0.4, 0.6]),
+                          out_scale=np.array([0.3, 0.2]), out_shift=np.zeros(2))
+    w = torch.tensor(surrogate.init_params(4), dtype=torch.float32, device=DEV)
+    nb = hpac.hpac_mlp_grad_blocks(n)
+    grad = torch.empty(nb * P, dtype=torch.float32, device=DEV)
+    loss = torch.full((nb,), SENTINEL, dtype=torch.float32, device=DEV)
+    say("max size: training gradient of %d items, %.0f GB of partials" % (n, grad.numel() * 4e-9))
+    hpac.hpac_mlp_grad(cols[:5], cols[5:], w, norm, n, grad, loss)
+    torch.cuda.synchronize()
+    assert not bool((loss == SENTINEL).any())
+    last = (1 << 22) - 1  # lanes of 2^22 workgroups: one more than a dispatch's count holds
+    for b0, b1 in ((0, 3), (last - 3, last + 3), (nb - 4, nb)):
+        part = [c[64 * b0:min(64 * b1, n)] for c in cols]
+        m = part[0].numel()
+        gp = torch.empty((b1 - b0) * P, dtype=torch.float32, device=DEV)
+        lp = torch.empty(b1 - b0, dtype=torch.float32, device=DEV)
+        hpac.hpac_mlp_grad(part[:5], part[5:], w, norm, n, gp, lp, n=m)
+        torch.cuda.synchronize()
+        assert torch.equal(gp, grad[b0 * P:b1 * P]) and torch.equal(lp, loss[b0:b1])
+    del cols, grad
+    torch.cuda.empty_cache()
