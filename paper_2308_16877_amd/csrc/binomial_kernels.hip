@@ -22,12 +22,12 @@
 //   * perforation: herded over the unit's option loop (small, large, ini,
 //     fini); a skipped option is neither read nor written.
 //
-// Bound by VALU issue.  65,536 American options on 512 steps: 2785 us when
+// Bound by VALU issue.  65,536 American options on 512 steps: 2772 us when
 // every step updated all 64 x 9 node slots of both values (9 instructions a
-// node), 522 us with the triangle of nodes, two instructions a node and the
-// European one of the two prices summed (6,450 VALU instructions per wave
-// against 43,000, 2.7 clocks each); 1023 steps 9694 -> 1496 us, 127 steps
-// 251 -> 116, 30 steps 85 -> 48; European 512 steps 1268 -> 103 us.
+// node), 481 us with the triangle of nodes, two instructions a node and the
+// European one of the two prices summed (6,435 VALU instructions per wave
+// against 43,000, 2.6 clocks each); 1023 steps 9694 -> 1494 us, 127 steps
+// 204 -> 94, 30 steps 68 -> 37; European 512 steps 1262 -> 98 us.
 #include "launch_binomial.hpp"
 #include <type_traits>
 #include "wave.hpp"
