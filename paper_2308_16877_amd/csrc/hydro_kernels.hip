@@ -677,9 +677,7 @@ __global__ void __launch_bounds__(256) k_hydro_node(HydroArgs a, HydroLoop lp) {
 // atomic.  kNoNext: the EOS alone.  A step on 90^3 elements takes 47.5 us
 // (30.2 this kernel, 16.6 the nodes: 186 and 109 MB counted, 6.2 and 6.6 TB/s)
 // against 61 in four launches, one on 24^3 with EOS TAF 11.1 against 17.  With
-// EOS TAF at thread level it takes 35.0 at 90^3, more than the exact one: a
-// wave that has one element to compute loads and computes as all of them do,
-// and the window is written beside; wave level 28.8.
+// EOS TAF at 90^3 this kernel takes 35.0 us at thread level, 28.8 at wave level.
 // Registers for three waves per SIMD, four where there are no hourglass
 // forces; with what the compiler takes by itself (172, two waves) EOS TAF at
 // 90^3 measured 12% slower.
